@@ -170,10 +170,10 @@ msm_status msm_compute(const msm_plan* plan, void* ws, size_t ws_bytes, msm_stre
  * for callers that cannot allocate device memory (code under stream capture,
  * tight serving loops, harnesses that forbid allocation).  Same arguments and
  * results as msm_compute minus ws/ws_bytes; every stage runs in order on
- * `stream`.  The workspace is a 64 MiB array in the library's device data,
- * one copy per GPU, held until the process ends; plans whose workspace
- * (msm_workspace_bytes) exceeds 64 MiB are rejected with MSM_ERR_UNSUPPORTED
- * before anything runs.  The array keeps the last call's contents: the first
+ * `stream`.  The workspace is a 65 MiB array (64 MiB and a plan's lattice
+ * weight fragments) in the library's device data, one copy per GPU, held until
+ * the process ends; plans whose workspace (msm_workspace_bytes) exceeds it are
+ * rejected with MSM_ERR_UNSUPPORTED before anything runs.  The array keeps the last call's contents: the first
  * call of a plan on a device (and the first after a re-tune, or after another
  * plan's call) uploads the plan's tables into it and synchronises `stream`.
  * All calls on one GPU share the array, so calls that overlap on one GPU (two
@@ -260,7 +260,7 @@ msm_status msm_profile_read(const msm_plan* plan, float* ms, int32_t* n_stages);
  * order.  In msm_plan_tune / msm_batch_tune a zero field keeps the current
  * value. */
 typedef struct msm_tuning {
-  int32_t lattice_b;     /* lattice-cutoff outputs per lane along x: 4, 6 or 8 */
+  int32_t lattice_b;     /* lattice-cutoff z planes per block: 4, 6 or 8 */
   int32_t item_chunks;   /* short-range 64-atom chunks of a cell row per work item (>= 1) */
   int32_t short_blocks;  /* blocks the short-range work items are strided over
                             (> 0), or -1 for one block per work item */

@@ -152,194 +152,182 @@ size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 
 bool finite_pos(double v) { return std::isfinite(v) && v > 0.0; }
 
-// Largest number of lanes of one half-wave (32 lanes) whose window offsets
-// fall in the same LDS bank (32 banks of 4 bytes).
-int bank_conflicts(int xl, int ty, int tz, int B, int px, int pp) {
-  int worst = 0;
-  for (int half = 0; half < 2; ++half) {
-    int cnt[32] = {0};
-    for (int l = half * 32; l < half * 32 + 32; ++l) {
-      const int xi = l % xl, yi = (l / xl) % ty, zi = l / (xl * ty);
-      if (zi >= tz) continue;
-      const int off = zi * pp + yi * px + xi * B;
-      worst = std::max(worst, ++cnt[off & 31]);
-    }
-  }
-  return worst;
+// Bits of the float16 nearest to v (ties to even; |v| below 65,520).
+uint16_t half_bits(double v) {
+  const uint16_t sign = std::signbit(v) ? 0x8000 : 0;
+  const double a = std::fabs(v);
+  if (a == 0.0) return sign;
+  int e = 0;
+  (void)std::frexp(a, &e);                                 // a in [2^(e-1), 2^e)
+  const int unit = std::max(e - 11, -24);                  // exponent of the last place
+  const int m = (int)std::nearbyint(std::ldexp(a, -unit)); // 11 bits at most, or 2^11 after rounding up
+  if (unit == -24) return (uint16_t)(sign | m);            // subnormal (2^10 becomes the smallest normal)
+  return (uint16_t)(sign | (((unit + 24) << 10) + m));     // the leading bit carries into the exponent
 }
 
-// Row and plane pitches (floats) of a window tile of `planes` z planes with
-// the fewest bank conflicts whose window still fits in max_floats.
-void pad_window(msm::LatTile& t, int B, int H, int planes, int max_floats) {
-  const int WX = t.xl * B + 2 * H, PY = t.ty + 2 * H;
-  int best = 1 << 30;
-  t.px = WX;
-  t.pp = PY * WX;
-  for (int px = WX; px < WX + 32; ++px)
-    for (int extra = 0; extra < 32; ++extra) {
-      const int pp = PY * px + extra;
-      if (planes * pp > max_floats) continue;
-      const int c = bank_conflicts(t.xl, t.ty, t.tz, B, px, pp);
-      const int score = c * 4096 + (pp * planes - WX * PY * planes) / 64;
-      if (score < best) {
-        best = score;
-        t.px = px;
-        t.pp = pp;
+double half_value(uint16_t h) {
+  const int e = (h >> 10) & 31, m = h & 1023;
+  const double v = e ? std::ldexp(1024.0 + m, e - 25) : std::ldexp((double)m, -24);
+  return (h & 0x8000) ? -v : v;
+}
+
+// Weight fragments of the tiled lattice-cutoff kernel for the taps W(|n|),
+// |n| < rad, n up to H per dimension; weight(n2) = W at |n|^2 = n2.  Lane l of a
+// fragment holds output l & 15 and 8 inputs from first(l / 16), zero where there
+// is no tap.  Fragments az (H + 1) + ay: the inputs within 8 of the outputs of
+// row (ay, az).  Then (H > 8), (2 phase + p)(H + 1) + ay further on: the wings
+// of the phase's planes 2p (lanes 0 - 31) and 2p + 1 (lanes 32 - 63).
+template <class Weight>
+void lattice_fragments(int H, double rad, Weight weight, msm::LatLaunch& lat, std::vector<uint16_t>& frags) {
+  auto inside = [&](int n2) { return std::sqrt((double)n2) < rad; };
+  double wmax = 0.0;
+  for (int n2 = 0; n2 <= 3 * H * H; ++n2)
+    if (inside(n2)) {
+      wmax = std::max(wmax, std::fabs(weight(n2)));
+      lat.n2max = n2;
+    }
+  int e = 0;
+  (void)std::frexp(wmax, &e);
+  lat.wexp = 14 - e;                                       // the largest weight lands in [2^13, 2^14)
+  lat.phases = (2 * H + msm::kLatPlanes) / msm::kLatPlanes;
+  const int words = msm::kLatFragBytes / 2, half = words / 2;
+  const int n_main = (H + msm::kLatPlanes) * (H + 1), n_wing = H > 8 ? 2 * lat.phases * (H + 1) : 0;
+  frags.assign((size_t)(n_main + n_wing) * words, 0);
+  auto octet = [&](int id, int quad, int first, int ay, int az) {
+    if (az > H) return;
+    for (int l = 16 * quad; l < 16 * quad + 16; ++l)
+      for (int i = 0; i < 8; ++i) {
+        const int nx = first + i - (l & 15), n2 = nx * nx + ay * ay + az * az;
+        if (std::abs(nx) > H || !inside(n2)) continue;
+        const double w = std::ldexp(weight(n2), lat.wexp);
+        const uint16_t hi = half_bits(w);
+        frags[(size_t)id * words + l * 8 + i] = hi;
+        frags[(size_t)id * words + half + l * 8 + i] = half_bits(w - half_value(hi));
       }
-    }
+  };
+  for (int az = 0; az <= H; ++az)                          // (the last phase's planes beyond H stay zero)
+    for (int ay = 0; ay <= H; ++ay)
+      for (int quad = 0; quad < 4; ++quad) octet(az * (H + 1) + ay, quad, 8 * quad - 8, ay, az);
+  if (n_wing)
+    for (int pp = 0; pp < 2 * lat.phases; ++pp)
+      for (int ay = 0; ay <= H; ++ay)
+        for (int quad = 0; quad < 4; ++quad)
+          octet(n_main + pp * (H + 1) + ay, quad, quad & 1 ? 24 : -16, ay, std::abs(2 * pp + quad / 2 - H));
 }
 
-// Split the compact rows (sorted by nz) into G contiguous nz ranges of nearly
-// equal work; grp[g] = first row of group g, grp[G] = number of rows.  Returns
-// the largest nz span (nz_hi - nz_lo) of a group.
-int split_rows(const std::vector<int4>& rows, int B, int G, short* grp) {
-  const int n = (int)rows.size();
-  std::vector<double> cost(n);
-  double total = 0.0;
-  for (int r = 0; r < n; ++r) {
-    const int xr = rows[r].z;
-    cost[r] = (2.0 * xr + 1.0) * B + (rows[r].y ? B + 2.0 * xr : 0.0) + 8.0;
-    total += cost[r];
-  }
-  int g = 0, span = 0, first = 0;
-  double acc = 0.0;
-  grp[0] = 0;
-  for (int r = 0; r < n; ++r) {
-    acc += cost[r];
-    const bool nz_ends = (r + 1 == n) || rows[r + 1].x != rows[r].x;
-    if (nz_ends && g + 1 < G && acc >= total * (g + 1) / G) {
-      grp[++g] = (short)(r + 1);
-      span = std::max(span, rows[r].x - rows[first].x);
-      first = r + 1;
-    }
-  }
-  span = std::max(span, rows[n - 1].x - rows[first].x);
-  while (g + 1 < G) grp[++g] = (short)n;        // fewer nz values than groups: empty groups
-  grp[G] = (short)n;
-  return span;
+// Whether row pair +-ay of a phase has taps (1), and wings as well (2).
+int lattice_row(const msm::LatLaunch& lat, int ph, int ay) {
+  const int nz0 = msm::kLatPlanes * ph - lat.H;
+  const int az = nz0 > 0 ? nz0 : std::max(0, -(nz0 + msm::kLatPlanes - 1));
+  const int n2 = ay * ay + az * az;
+  return n2 > lat.n2max ? 0 : (lat.H > 8 && 81 + n2 <= lat.n2max ? 2 : 1);
 }
 
-// Tile shapes and row groups of the windowed lattice-cutoff kernel.  For each
-// candidate B (outputs per lane along x) and each sub-top level, pick
-// (xl, ty, tz) lanes minimising a per-tile cost in wave instructions (FMA
-// slots including ragged-tile waste, about half a FMA per tap with mirror-row
-// pairing, plus the window load).  Then split the rows of each tile into
-// groups so that the blocks of a launch (level 0 alone; levels 1 .. l-2
-// together) cover the 256 compute units with short blocks: the launch is
-// estimated as ceil(blocks / 256) times its longest block.
-void choose_lattice_tiles(const Geom& g, const std::vector<int4>& rows, int taps, int H_,
-                          int tables_bytes, msm::LatLaunch& lat, int force_b = 0, int force_waves = 0) {
-  const int n_rows = lat.n_rows, n_wc = lat.n_wc;
+// Cuts the rows of a phase into contiguous shares of 4 waves with the least
+// largest cost, which it returns (fragment pairs; wings count half).
+double cut_rows(msm::LatLaunch& lat, int ph) {
+  constexpr int waves = 4;
+  std::vector<double> cost;
+  for (int ay = 0; ay <= lat.H; ++ay) {
+    const int kind = lattice_row(lat, ph, ay);
+    if (kind == 0) break;
+    for (int sgn = 0; sgn < (ay ? 2 : 1); ++sgn) cost.push_back(kind == 2 ? 1.5 : 1.0);
+  }
+  auto shares = [&](double cap, unsigned char* cut) {
+    int w = 0;
+    double acc = 0.0;
+    cut[0] = 0;
+    for (size_t i = 0; i < cost.size(); ++i) {
+      if (acc + cost[i] > cap + 1e-9) {
+        if (++w == waves) return false;
+        cut[w] = (unsigned char)i;
+        acc = 0.0;
+      }
+      acc += cost[i];
+    }
+    while (w < waves) cut[++w] = (unsigned char)cost.size();
+    return true;
+  };
+  double lo = 0.0, hi = 0.0;
+  for (double c : cost) hi += c;
+  unsigned char scratch[sizeof(lat.cut[0])];
+  for (int it = 0; it < 40; ++it) {                        // bisection
+    const double mid = 0.5 * (lo + hi);
+    (shares(mid, scratch) ? hi : lo) = mid;
+  }
+  shares(hi, lat.cut[ph]);
+  return hi;
+}
+
+// Tiles of the lattice-cutoff kernel: planes per block (force_b, or by the
+// rule below), the phases' rows cut into the waves' shares, and the split of
+// each level's phases over blocks: more blocks fill the chip, fewer write and
+// read back fewer partials.  The estimate in cycles: a block starts and ends
+// (9,000), each phase stages its window and runs its rows on the matrix pipe,
+// 48 cycles a fragment pair; the work is spread over the blocks that fit the
+// 256 compute units, plus the longest block.  100,000-atom box, level 0 in 1, 2,
+// 3, 5 blocks per tile: 78, 47, 43, 44 us; 1M box in 1, 2, 3, 5: 105, 116, 111, 115.
+void choose_lattice_tiles(const Geom& g, int H_, msm::LatLaunch& lat, int force_b = 0) {
+  const int phases = lat.phases, wexp = lat.wexp, n2max = lat.n2max;
   std::memset(&lat, 0, sizeof(lat));
   lat.H = H_;
-  lat.n_rows = n_rows;
-  lat.n_wc = n_wc;
+  lat.phases = phases;
+  lat.wexp = wexp;
+  lat.n2max = n2max;
   if (g.levels < 2 || H_ > msm::kLatMaxHalo) return;
-  const int max_floats = (msm::kLatMaxLds - tables_bytes) / 4;
-  // periodic levels get their ghost copies from u^{k,cut} itself: no row groups
-  const int gmax = g.periodic ? 1 : std::min(msm::kLatMaxGroups, 2 * H_ + 1);
-  double best = 1e300;
-  msm::LatLaunch cand;
-  const int Bs[3] = {4, 6, 8};
-  for (int bi = 0; bi < 3; ++bi) {
-    const int B = Bs[bi];
-    if (force_b && B != force_b) continue;
-    cand = lat;
-    cand.b = B;
-    cand.n = g.levels - 1;
-    int span[msm::kLatMaxGroups + 1] = {};
-    for (int G = 1; G <= gmax; ++G) span[G] = split_rows(rows, B, G, cand.grp[G]);
-    // per level: best tile by per-tile cost (all groups)
-    double tile_cost[msm::kMaxLevels] = {};
-    long long tiles[msm::kMaxLevels] = {};
-    bool ok = true;
-    for (int k = 0; k < g.levels - 1; ++k) {
-      const msm::Level& L = g.lv[k];
-      double lbest = 1e300;
-      msm::LatTile tb{};
-      for (int tz = 1; tz <= 16; ++tz)
-        for (int ty = 1; ty <= 16; ++ty)
-          for (int xl = 1; xl <= 16; ++xl) {
-            if (xl * ty * tz > 64 || xl * ty * tz < 32) continue;
-            const int WX = xl * B + 2 * H_, PY = ty + 2 * H_, WZ = tz + 2 * H_;
-            if (WZ * PY * WX > max_floats) continue;
-            const long long nt = (long long)((L.n[0] + xl * B - 1) / (xl * B)) *
-                                 ((L.n[1] + ty - 1) / ty) * ((L.n[2] + tz - 1) / tz);
-            const double c = (double)nt * (0.55 * B * taps + (double)WZ * PY * WX / 16.0);
-            if (c < lbest) {
-              lbest = c;
-              tb = msm::LatTile{k, xl, ty, tz, (L.n[0] + xl * B - 1) / (xl * B), (L.n[1] + ty - 1) / ty,
-                                (L.n[2] + tz - 1) / tz, 0, WX, WX * PY, 1, 0};
-            }
-          }
-      if (lbest >= 1e300) {
-        ok = false;
-        break;
+  const int skip = g.periodic ? g.ghost : 0;
+  auto tiles_of = [&](int k, int B, msm::LatTile& t) {
+    // a periodic level's outputs: the nodes of one period, along x from the
+    // multiple of 8 below its first
+    const msm::Level& L = g.lv[k];
+    t.ntx = ((g.periodic ? L.per[0] + (skip & 7) : L.n[0]) + 15) / 16;
+    t.nty = (L.n[1] - 2 * skip + 15) / 16;
+    t.ntz = (L.n[2] - 2 * skip + B - 1) / B;
+    return (double)t.ntx * t.nty * t.ntz;
+  };
+  // 6 planes unless that leaves the chip mostly empty (fewer than 128 blocks on
+  // level 0), where 4 fill it better: 24,000-atom box (324 blocks) 28.8 us with
+  // 4, 23.1 with 6, 32.4 with 8 planes; 9,000-atom periodic box (96 blocks)
+  // 22.5, 24.3 and 24.4; 1,000 charges (8 blocks) 11.6, 12.4 and 13.4
+  msm::LatTile probe{};
+  const int B = force_b ? force_b : (tiles_of(0, 6, probe) * phases < 128.0 ? 4 : 6);
+  lat.b = B;
+  lat.n = g.levels - 1;
+  lat.lds_bytes = msm::lat_lds(H_, B);
+  std::vector<double> mat(phases);                         // fragment pairs of each phase's slowest wave
+  for (int ph = 0; ph < phases; ++ph) mat[ph] = cut_rows(lat, ph);
+  // the partials live where the anterpolation's did, or in 8 MiB
+  const double part_cap = std::max((double)g.atn[0] * g.atn[1] * g.atn[2] * g.at_ext, 1048576.0);
+  // blocks on the chip at a time (two on a CU share its matrix pipes)
+  const int slots = 256 * (B < 8 && 2 * (lat.lds_bytes + 4096) <= 160 * 1024 ? 2 : 1);
+  int blocks = 0;
+  for (int k = 0; k < g.levels - 1; ++k) {
+    const msm::Level& L = g.lv[k];
+    msm::LatTile t{};
+    t.level = k;
+    const double tiles = tiles_of(k, B, t);
+    double best = 1e300;
+    for (int G = 1; G <= std::min(msm::kLatMaxGroups, phases); ++G) {
+      if (G > 1 && lat.n_part + (double)G * L.count > part_cap) break;
+      double sum = 0.0, longest = 0.0;
+      for (int q = 0; q < G; ++q) {
+        double blk = 9000.0;
+        for (int ph = phases * q / G; ph < phases * (q + 1) / G; ++ph)
+          blk += 3000.0 + 500.0 * (B + 3) + mat[ph] * 48.0 * msm::kLatPlanes * B * (slots / 256);
+        sum += blk;
+        longest = std::max(longest, blk);
       }
-      cand.t[k] = tb;
-      tiles[k] = (long long)tb.ntx * tb.nty * tb.ntz;
-      tile_cost[k] = lbest / (double)tiles[k];
+      const double est = tiles * sum / slots + longest + (G > 1 ? 0.013 * G * L.count : 0.0);
+      if (est < best) {
+        best = est;
+        t.groups = G;
+      }
     }
-    if (!ok) continue;
-    // cost of one block of level k with G groups
-    auto block_cost = [&](int k, int G) {
-      const msm::LatTile& t = cand.t[k];
-      const int WX = t.xl * B + 2 * H_, PY = t.ty + 2 * H_;
-      const double stage = (double)(t.tz + span[G]) * PY * WX / 16.0;
-      return 0.55 * B * taps / G + stage + 300.0;
-    };
-    // groups per level for one launch over levels [k0, k1): a common target
-    // block cost tau sets G_k = ceil(cost_k(1) / tau)
-    auto choose_groups = [&](int k0, int k1) {
-      double est_best = 1e300;
-      int gbest[msm::kMaxLevels] = {};
-      for (int kk = k0; kk < k1; ++kk)
-        for (int G = 1; G <= gmax; ++G) {
-          const double tau = block_cost(kk, G);
-          int gk[msm::kMaxLevels] = {};
-          long long blocks = 0;
-          double longest = 0.0;
-          for (int k = k0; k < k1; ++k) {
-            int Gk = 1;
-            while (Gk < gmax && block_cost(k, Gk) > tau) ++Gk;
-            gk[k] = Gk;
-            blocks += tiles[k] * Gk;
-            longest = std::max(longest, block_cost(k, Gk));
-          }
-          const double est = (double)((blocks + 255) / 256) * longest;
-          if (est < est_best) {
-            est_best = est;
-            std::copy(gk, gk + msm::kMaxLevels, gbest);
-          }
-        }
-      for (int k = k0; k < k1; ++k) cand.t[k].groups = gbest[k];
-      return est_best;
-    };
-    const double est = choose_groups(0, 1) + (g.levels > 2 ? choose_groups(1, g.levels - 1) : 0.0);
-    // waves per block: a grid of many tiles balances its stencil rows better
-    // over fewer waves per tile; a grid of few tiles needs every tile's waves
-    cand.waves = force_waves ? force_waves
-                             : (tiles[0] >= msm::kLatWavesTiles ? msm::kLatWavesFew : msm::kLatWavesMany);
-    // padding, LDS, block and partial offsets
-    long long blocks = 0;
-    int lds_max = 0, part = 0;
-    for (int k = 0; k < g.levels - 1; ++k) {
-      msm::LatTile& t = cand.t[k];
-      const int planes = t.tz + span[t.groups];
-      pad_window(t, B, H_, planes, max_floats);
-      const int lds = std::max(tables_bytes + planes * t.pp * 4, cand.waves * 64 * B * 8);
-      lds_max = std::max(lds_max, lds);
-      t.block0 = (int)blocks;
-      blocks += tiles[k] * t.groups;
-      t.part0 = part;
-      if (t.groups > 1) part += t.groups * g.lv[k].count;
-    }
-    cand.lds_bytes = lds_max;
-    cand.n_part = part;
-    if (est < best) {
-      best = est;
-      lat = cand;
-    }
+    t.block0 = blocks;
+    blocks += t.ntx * t.nty * t.ntz * t.groups;
+    t.part0 = lat.n_part;
+    if (t.groups > 1) lat.n_part += t.groups * L.count;
+    lat.t[k] = t;
   }
 }
 
@@ -442,7 +430,6 @@ void refresh_launch(msm_plan* P) {
   lg.m = g.m;
   lg.pair = g.pair;
   lg.lat_b = P->lat.b;
-  lg.lat_waves = P->lat.b ? P->lat.waves : msm::kLatWavesMany;
   lg.lat_lds = P->lat.lds_bytes;
   lg.max_levels = g.levels;
   lg.streams = P->streams;
@@ -620,19 +607,10 @@ void set_cell_geometry(msm_plan* P, int reach) {
 // tries the finer cells.
 int default_reach(int) { return 2; }
 
-void set_lattice_waves(msm_plan* P, int waves) {
-  P->lat_waves = waves;
-  if (P->lat.b > 0 && P->lat.waves != waves) {
-    choose_lattice_tiles(P->g, P->rows_c, (int)P->weights.size(), P->lat.H, P->lat_tables, P->lat, P->lat.b, waves);
-    refresh_launch(P);
-  }
-}
-
 void retune(msm_plan* P, const msm_tuning& t) {
   if (t.cell_reach != 0 && t.cell_reach != P->g.reach) set_cell_geometry(P, t.cell_reach);
   if (t.lattice_b && P->lat.b && t.lattice_b != P->lat.b)
-    choose_lattice_tiles(P->g, P->rows_c, (int)P->weights.size(), P->lat.H, P->lat_tables, P->lat,
-                         t.lattice_b, P->lat_waves);
+    choose_lattice_tiles(P->g, P->lat.H, P->lat, t.lattice_b);
   Geom& g = P->g;
   if (t.item_chunks > 0) set_row_items(g, t.item_chunks);
   if (t.short_blocks != 0) P->short_cap = t.short_blocks < 0 ? 0 : t.short_blocks;
@@ -691,11 +669,10 @@ msm::DevPtrs dev_ptrs(const msm_plan* P, void* ws) {
   d.ant_part = (decltype(d.ant_part))(b + o[msm::kSecAntPart]);
   d.rows = (decltype(d.rows))(b + o[msm::kSecRows]);
   d.weights = (decltype(d.weights))(b + o[msm::kSecWeights]);
-  d.rows_c = (decltype(d.rows_c))(b + o[msm::kSecRowsC]);
-  d.weights_c = (decltype(d.weights_c))(b + o[msm::kSecWeightsC]);
+  d.lat_frags = (decltype(d.lat_frags))(b + o[msm::kSecLatFrags]);
   d.top = (decltype(d.top))(b + o[msm::kSecTop]);
   d.partials = (decltype(d.partials))(b + o[msm::kSecPartials]);
-  d.lat_part = (decltype(d.lat_part))(b + o[msm::kSecLatPart]);
+  d.lat_part = (decltype(d.lat_part))(b + o[msm::kSecAntPart]);
   d.excl_start = (decltype(d.excl_start))(P->excl_start);
   d.excl_idx = (decltype(d.excl_idx))(P->excl_idx);
   d.excl_nnz = P->excl_nnz;
@@ -932,48 +909,22 @@ msm_status msm_plan_create(const msm_params* prm, int32_t n_atoms, msm_plan** ou
         P->rows.push_back(row);
       }
   }
-  // compact stencil for the windowed kernel: for |nz|, ny >= 0 the weights
-  // W(nx) for nx = 0..xr (padded to a multiple of 4); rows for nz in [-H, H]
+  // weight fragments of the tiled kernel
   if (L > 1) {
     int H = 0;
     for (const auto& r : P->rows) H = std::max(H, std::abs(r.nx));
     if (H <= msm::kLatMaxHalo) {
-      auto xrow = [&](int az, int ay) {
-        int xr = -1;
-        for (int nx = 0; nx <= H; ++nx)
-          if (h * std::sqrt((double)(nx * nx + ay * ay + az * az)) < 2.0 * a) xr = nx;
-        return xr;
+      auto weight = [&](int n2) {
+        const double dist = h * std::sqrt((double)n2);
+        return gamma_h(c, g.m, dist / a) / a - gamma_h(c, g.m, dist / (2.0 * a)) / (2.0 * a);
       };
-      std::vector<int> woff((size_t)(H + 1) * (H + 1), -1);
-      for (int az = 0; az <= H; ++az)
-        for (int ay = 0; ay <= H; ++ay) {
-          const int xr = xrow(az, ay);
-          if (xr < 0) continue;
-          woff[(size_t)az * (H + 1) + ay] = (int)P->weights_c.size();
-          for (int nx = 0; nx <= xr; ++nx) {
-            const double dist = h * std::sqrt((double)(nx * nx + ay * ay + az * az));
-            P->weights_c.push_back((float)(gamma_h(c, g.m, dist / a) / a -
-                                           gamma_h(c, g.m, dist / (2.0 * a)) / (2.0 * a)));
-          }
-          while (P->weights_c.size() % 4) P->weights_c.push_back(0.f);
-        }
-      for (int nz = -H; nz <= H; ++nz)
-        for (int ay = 0; ay <= H; ++ay) {
-          const int az = std::abs(nz);
-          const int xr = xrow(az, ay);
-          if (xr >= 0) P->rows_c.push_back(make_int4(nz, ay, xr, woff[(size_t)az * (H + 1) + ay]));
-        }
-      P->lat.n_rows = (int)P->rows_c.size();
-      P->lat.n_wc = (int)P->weights_c.size();
-      const int tables = P->lat.n_rows * 16 + P->lat.n_wc * 4;
-      P->lat_tables = tables;
+      lattice_fragments(H, 2.0 * a / h, weight, P->lat, P->lat_frags);
       // the partials section holds the largest need of any tuning
-      for (int b : {4, 6, 8})
-        for (int w : {msm::kLatWavesFew, msm::kLatWavesMany}) {
-          choose_lattice_tiles(g, P->rows_c, (int)P->weights.size(), H, tables, P->lat, b, w);
-          P->lat_part_max = std::max(P->lat_part_max, P->lat.n_part);
-        }
-      choose_lattice_tiles(g, P->rows_c, (int)P->weights.size(), H, tables, P->lat, 0, P->lat_waves);
+      for (int b : {4, 6, 8}) {
+        choose_lattice_tiles(g, H, P->lat, b);
+        P->lat_part_max = std::max(P->lat_part_max, P->lat.n_part);
+      }
+      choose_lattice_tiles(g, H, P->lat);
     } else {
       P->lat.b = 0;
       P->lat.H = H;
@@ -1018,14 +969,15 @@ msm_status msm_plan_create(const msm_params* prm, int32_t n_atoms, msm_plan** ou
   lay.bytes[msm::kSecBinHist] = std::max<size_t>((size_t)P->max_bin_hist, 1) * sizeof(int);
   // tile totals of the four-kernel binning's scan, or the row starts of the row binning
   lay.bytes[msm::kSecScan] = ((size_t)P->max_cells + 1) * sizeof(int);
-  lay.bytes[msm::kSecAntPart] = (size_t)g.atn[0] * g.atn[1] * g.atn[2] * g.at_ext * sizeof(long long);
+  // the anterpolation's partials and, once q^0 is gathered from them, the
+  // lattice cutoff's share one section
+  lay.bytes[msm::kSecAntPart] = std::max((size_t)g.atn[0] * g.atn[1] * g.atn[2] * g.at_ext * sizeof(long long),
+                                         P->lat_part_max * sizeof(double));
   lay.bytes[msm::kSecRows] = std::max<size_t>(P->rows.size(), 1) * sizeof(msm::StencilRow);
   lay.bytes[msm::kSecWeights] = std::max<size_t>(P->weights.size(), 1) * sizeof(float);
-  lay.bytes[msm::kSecRowsC] = std::max<size_t>(P->rows_c.size(), 1) * sizeof(int4);
-  lay.bytes[msm::kSecWeightsC] = std::max<size_t>(P->weights_c.size(), 1) * sizeof(float);
+  lay.bytes[msm::kSecLatFrags] = std::max<size_t>(P->lat_frags.size(), 1) * sizeof(uint16_t);
   lay.bytes[msm::kSecTop] = P->top.size() * sizeof(double);
   lay.bytes[msm::kSecPartials] = 10 * (size_t)P->n_partials * sizeof(double);
-  lay.bytes[msm::kSecLatPart] = std::max<size_t>(P->lat_part_max, 1) * sizeof(double);
   lay.bytes[msm::kSecDesc] = sizeof(msm::SysDesc);
   size_t o = 0;
   for (int s = 0; s < msm::kSecCount; ++s) {
@@ -1176,15 +1128,13 @@ msm_status msm_plan_describe(const msm_plan* P, char* buf, size_t buf_bytes) {
        ", \"streams\": " + std::to_string(P->streams) + ", \"short_after\": " + std::to_string(P->short_after) +
        ", \"short_split\": " + std::to_string(P->short_split);
   o += ", \"taps\": " + std::to_string(P->weights.size()) + ", \"halo\": " + std::to_string(P->lat.H);
-  o += ", \"lattice_b\": " + std::to_string(P->lat.b) + ", \"lattice_waves\": " + std::to_string(P->lat.waves) +
+  o += ", \"lattice_b\": " + std::to_string(P->lat.b) + ", \"lattice_waves\": " + std::to_string(P->lat.b > 0 ? msm::lat_waves(P->lat.b) : 0) +
        ", \"lattice_lds\": " +
        std::to_string(P->lat.lds_bytes) + ", \"lattice_tiles\": [";
   for (int k = 0; k < P->lat.n; ++k) {
     const msm::LatTile& t = P->lat.t[k];
     if (k) o += ", ";
-    o += "[" + std::to_string(t.xl) + ", " + std::to_string(t.ty) + ", " + std::to_string(t.tz) + ", " +
-         std::to_string(t.ntx * t.nty * t.ntz) + ", " +
-         std::to_string(bank_conflicts(t.xl, t.ty, t.tz, P->lat.b, t.px, t.pp)) + ", " +
+    o += "[16, 16, " + std::to_string(P->lat.b) + ", " + std::to_string(t.ntx * t.nty * t.ntz) + ", " +
          std::to_string(t.groups) + "]";
   }
   o += "], \"prolong_per_level\": " + std::to_string(P->lg.prolong_split ? 1 : 0);
@@ -1225,13 +1175,10 @@ msm_status init_workspace(const msm_plan* P, void* ws, hipStream_t s) {
     e = hipMemcpyAsync(base + P->lay.off[msm::kSecWeights], P->weights.data(),
                        P->weights.size() * sizeof(float), hipMemcpyHostToDevice, s);
     if (e != hipSuccess) return hip_fail(e, "upload stencil weights");
-    if (!P->rows_c.empty()) {
-      e = hipMemcpyAsync(base + P->lay.off[msm::kSecRowsC], P->rows_c.data(),
-                         P->rows_c.size() * sizeof(int4), hipMemcpyHostToDevice, s);
-      if (e != hipSuccess) return hip_fail(e, "upload compact stencil rows");
-      e = hipMemcpyAsync(base + P->lay.off[msm::kSecWeightsC], P->weights_c.data(),
-                         P->weights_c.size() * sizeof(float), hipMemcpyHostToDevice, s);
-      if (e != hipSuccess) return hip_fail(e, "upload compact stencil weights");
+    if (!P->lat_frags.empty()) {
+      e = hipMemcpyAsync(base + P->lay.off[msm::kSecLatFrags], P->lat_frags.data(),
+                         P->lat_frags.size() * sizeof(uint16_t), hipMemcpyHostToDevice, s);
+      if (e != hipSuccess) return hip_fail(e, "upload stencil fragments");
     }
   }
   e = hipMemcpyAsync(base + P->lay.off[msm::kSecTop], P->top.data(), P->top.size() * sizeof(double),

@@ -107,41 +107,58 @@ struct StencilRow {
   int nx, ny, zr, woff;
 };
 
-// Windowed lattice-cutoff launch: one tile shape per sub-top level.  A tile's
-// stencil rows may be split into `groups` contiguous ranges of nz, one block
-// each; each such block then writes float64 partial sums per node, which the
-// consumers of u^{k,cut} add in group order.
+// Tiled lattice-cutoff launch (matrix instructions): a block owns 16 x 16 x b
+// nodes (x, y, z) of a sub-top level.  The stencil planes nz = -H .. H are
+// taken in phases of kLatPlanes, each with its own input window in LDS; the
+// block's waves split a phase's rows.  A tile's phases may be split into
+// `groups` contiguous ranges, one block each; each such block then writes
+// float64 partial sums per node, which the consumers of u^{k,cut} add in group
+// order.
 struct LatTile {
   int level;
-  int xl, ty, tz;          // lanes along x (B outputs each), y, z
   int ntx, nty, ntz;       // tiles per dimension
   int block0;              // first block of this level
-  int px;                  // padded LDS row pitch of the window (floats)
-  int pp;                  // padded LDS plane pitch of the window (floats)
-  int groups;              // row groups per tile (1: the block writes u^{k,cut} itself)
+  int groups;              // phase groups per tile (1: the block writes u^{k,cut} itself)
   int part0;               // first float64 partial of this level (groups * nodes of the level)
 };
 
-constexpr int kLatMaxHalo = 16;          // windowed kernel handles stencil half-widths up to this
-constexpr int kLatMaxLds = 150 * 1024;   // LDS budget of one windowed block (bytes)
-constexpr int kLatWavesFew = 8;          // waves per windowed block for grids of many tiles
-constexpr int kLatWavesMany = 16;        // and for grids of few tiles (their totals meet in LDS)
-constexpr int kLatWavesTiles = 1024;     // level-0 tiles from which the smaller blocks are used
-constexpr int kLatMaxGroups = 8;         // row groups per tile
+constexpr int kLatMaxHalo = 13;          // tiled kernel handles stencil half-widths up to this
+constexpr int kLatPlanes = 4;            // stencil planes per phase
+// Waves per block: 4 for up to 6 planes (two blocks per CU where the window
+// allows), two groups of 4 for 8 planes, whose window leaves room for one block.
+__host__ __device__ constexpr int lat_waves(int b) { return b == 8 ? 8 : 4; }
+constexpr int kLatMaxPhases = (2 * kLatMaxHalo + kLatPlanes) / kLatPlanes;
+constexpr int kLatMaxGroups = 8;         // phase groups per tile
+constexpr int kLatFragBytes = 2048;      // weight fragment: float16 high and low parts of 16 x 32 weights
 
 struct LatLaunch {
-  int b;                   // outputs per lane along x (template), 0 = use the untiled kernel
+  int b;                   // z planes per block (template), 0 = use the untiled kernel
   int n;                   // levels in the launch
   int H;                   // stencil half-width in nodes
   int lds_bytes;           // dynamic LDS per block
-  int n_rows;              // compact rows (nz in [-H, H], ny >= 0)
-  int n_wc;                // compact weights (floats, each row padded to a multiple of 4)
+  int phases;              // groups of kLatPlanes stencil planes
+  int wexp;                // weights are stored times 2^wexp
+  int n2max;               // largest |n|^2 of a tap
   int n_part;              // float64 partials of every grouped level
-  int waves;               // waves per block (kLatWavesFew or kLatWavesMany)
-  // first compact row of group g when a tile has G groups: grp[G][g], g <= G
-  short grp[kLatMaxGroups + 1][kLatMaxGroups + 1];
+  // row i of a phase is ny = 0 (i = 0), (i + 1) / 2 (odd i) or -(i + 1) / 2;
+  // wave w of a group of 4 takes rows cut[phase][w] .. cut[phase][w + 1] - 1
+  unsigned char cut[kLatMaxPhases][8];
   LatTile t[kMaxLevels];
 };
+
+// Input window of one phase of a tile: octets (8 x values) per row, row pitch
+// in values (an odd multiple of 8: the 16 rows of a fragment then start in
+// distinct LDS bank groups) and rows; one octet of every row per thread.
+__host__ __device__ inline int lat_left(int H) { return H > 8 ? 2 : 1; }            // octets left of the tile
+__host__ __device__ inline int lat_octets(int H) { return 2 + 2 * lat_left(H); }
+__host__ __device__ inline int lat_pitch(int H) { return 8 * lat_octets(H) + 8; }
+__host__ __device__ inline int lat_rows(int H) { return 16 + 2 * H; }
+static_assert((16 + 2 * kLatMaxHalo) * 6 <= 256, "a thread (of 256) per octet of a plane");
+// high and low halves of the window, or the waves' float64 totals
+__host__ __device__ inline int lat_lds(int H, int b) {
+  const int win = (b + kLatPlanes - 1) * lat_rows(H) * lat_pitch(H) * 4, red = 4 * 64 * 4 * b * 8;
+  return win > red ? win : red;
+}
 
 // Workspace sections (in order).  Offsets are 256-byte aligned.
 enum Section : int {
@@ -159,14 +176,13 @@ enum Section : int {
   kSecTmp,            // int[n]
   kSecBinHist,        // int[bin_blocks * n_cells]: per-block cell counts (two-kernel binning)
   kSecScan,           // int[scan tiles]: cell counts per tile of the four-kernel binning's scan
-  kSecAntPart,        // int64[anterpolation tiles * at_ext]: fixed-point private regions of the tiles
+  kSecAntPart,        // int64[anterpolation tiles * at_ext]: fixed-point private regions of the tiles, then
+                      // double[]: phase-group partials of the lattice cutoff
   kSecRows,           // StencilRow[n_rows]
   kSecWeights,        // float[n_weights]
-  kSecRowsC,          // int4[n_rows]: compact rows (nz, ny >= 0, xr, weight offset)
-  kSecWeightsC,       // float[n_wc]: W(nx, ny, |nz|) for nx = 0..xr per compact row
+  kSecLatFrags,       // float16 weight fragments of the tiled lattice kernel
   kSecTop,            // double[top table]
   kSecPartials,       // double[10 * n_partials]: energy, then 9 virial components
-  kSecLatPart,        // double[]: row-group partials of the lattice cutoff
   kSecDesc,           // SysDesc: this workspace's descriptor (pointers into it)
   kSecCount
 };
@@ -204,8 +220,7 @@ struct DevPtrs {
   MSM_GLOBAL int* scan;
   MSM_GLOBAL long long* ant_part;
   MSM_GLOBAL const StencilRow* rows;
-  MSM_GLOBAL const int4* rows_c;
-  MSM_GLOBAL const float* weights_c;
+  MSM_GLOBAL const uint4* lat_frags;
   MSM_GLOBAL const float* weights;
   MSM_GLOBAL const double* top;
   MSM_GLOBAL double* partials;
@@ -302,9 +317,8 @@ struct LaunchGeom {
   int order = 4;                     // common to every system of a launch
   int m = 2;
   int pair = kPairMsm;               // pair method (common to every system of a launch)
-  int lat_b = 0;                     // windowed lattice outputs per lane, 0 = untiled kernel
-  int lat_waves = kLatWavesMany;     // waves per windowed lattice block
-  int lat_lds = 0;                   // dynamic LDS of the windowed kernel
+  int lat_b = 0;                     // z planes per wave of the tiled lattice kernel, 0 = untiled kernel
+  int lat_lds = 0;                   // dynamic LDS of the tiled kernel
   int max_levels = 1;
   int streams = 3;                   // 1: in order; 2: short range on a side stream; 3: also level-0 lattice
   int short_after = 1;               // side-stream short range starts after 1: binning, 2: anterpolation,

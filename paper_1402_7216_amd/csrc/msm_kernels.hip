@@ -2152,18 +2152,6 @@ __global__ void __launch_bounds__(kBlock) k_top(KArgs A) {
   top_node(S, node, threadIdx.x & (kWave - 1));
 }
 
-// Blocks of a lattice-cutoff launch of a system.  part 0: the level-0 tiles;
-// part 1: the coarse tiles (levels 1 .. l-2) then kLatWaves top-level nodes
-// per block; part 2: every tile then the top level (one launch when level 0
-// has no stream of its own).  first = first tile block of the part.
-__device__ __forceinline__ int lattice_tile_blocks(const LatLaunch& P, int part, int& first) {
-  const LatTile& t = P.t[P.n - 1];
-  const int total = t.block0 + t.ntx * t.nty * t.ntz * t.groups;
-  const int b1 = P.n > 1 ? P.t[1].block0 : total;
-  first = (part == 1) ? b1 : 0;
-  return (part == 0) ? b1 : (part == 1 ? total - b1 : total);
-}
-
 // --------------------------------------------------------------------------
 // Lattice cutoff (itemised algorithm) for every level k <= l-2 in one launch:
 //   u^{k,cut}_mu = sum_{|n| < 2a/h} g^k(2^k h |n|) q^k_{mu+n} = 2^-k sum W(n) q^k_{mu+n}
@@ -2207,222 +2195,326 @@ __global__ void __launch_bounds__(kBlock) k_lattice(KArgs A, int part) {
 }
 
 // --------------------------------------------------------------------------
-// Lattice cutoff, windowed (same sum as k_lattice).  One block = one output
-// tile of one level: xl lanes along x (B consecutive outputs each, kept in
-// registers), ty along y, tz along z.  The block stages its whole input
-// window ((tz + 2H) x (ty + 2H) x (xl B + 2H), zero outside the grid) in LDS
-// once, together with the stencil in compact form, then its 8 waves split a
-// flat list of stencil rows with no further barriers.
+// Lattice cutoff on the matrix cores (same sum as k_lattice).  For one stencil
+// row (ny, nz) the 16 outputs along x of a node row are a 16 x 32 Toeplitz
+// matrix of weights, A[m][k] = W(k - 8 - m, ny, nz), times the 32 inputs
+// around them; 16 node rows (y) make the columns: one 16x16x32 MFMA per row
+// and plane, and half a second one (the wing) for rows with more than 8 taps
+// to a side.  Weights and inputs are split into two float16 numbers each (x s =
+// hi + lo with s a power of two, 22 bits; the inputs' s from the largest |q| of
+// the staged window, so nothing overflows and values down to 2^-38 of it
+// count), and the products hi hi + hi lo + lo hi are exact in float32; the sums
+// are flushed to float64 after every pair of rows +-ny of 4 planes.
 //
-// Compact stencil: W depends on |n| only, so a row (nz, ny) with taps
-// nx in [-xr, xr] stores W for nx = 0..xr, shared by nz and -nz; and rows
-// (nz, +ny), (nz, -ny) are processed together by adding their inputs first
-// (one FMA chain for both).
+// A block owns 16 x 16 x ZB nodes.  A phase takes 4 planes nz: its input planes
+// are staged once (split into the two halves on the way, zero outside the
+// grid), and every staged fragment of a row (16 bytes per lane and half) serves
+// the 4 planes it is an input of, so the matrix pipe, not LDS, is the limit:
+// 12 MFMAs per 2 LDS reads.  The 4 waves split the phase's rows.  The weights'
+// fragments come from the L2 (the same for every block); +ny and -ny share them.
 // --------------------------------------------------------------------------
+typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+typedef _Float16 half2v __attribute__((ext_vector_type(2)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+struct __attribute__((packed, aligned(4))) float4_a4 {
+  float v[4];
+};
 
-template <int B, int XR, bool PAIR>
-__device__ __forceinline__ void row_win(float* acc, const float* a, const float* b,
-                                        const float* wrow) {
-  // taps in groups of 4: each group reads the 4 window values (and weights) it
-  // adds to the window, and the scheduler keeps the groups apart, so a lane
-  // holds about B + 8 values instead of the whole row (8 waves per SIMD fit)
-  constexpr int NT = 2 * XR + 1;
-  float v[B + 2 * XR];
+// acc[z] += the 4 planes' fragments (weights ah, al) against the staged input
+// planes [zlo, zhi) (hi, lo; `plane` values apart) of one row of ZB output
+// planes: input plane zi is plane j's input of output zi - j.
+template <int ZB>
+__device__ __forceinline__ void lat_row(floatx4* acc, const half8* ah, const half8* al, const _Float16* hi,
+                                        const _Float16* lo, int plane, int zlo, int zhi) {
+  half8 nh = *reinterpret_cast<const half8*>(hi), nl = *reinterpret_cast<const half8*>(lo);
 #pragma unroll
-  for (int j = 0; j < B - 1; ++j) v[j] = PAIR ? a[j] + b[j] : a[j];
-#pragma unroll
-  for (int t0 = 0; t0 < NT; t0 += 4) {
-    float w[4];
-#pragma unroll
-    for (int t = t0; t < t0 + 4 && t < NT; ++t) {
-      v[t + B - 1] = PAIR ? a[t + B - 1] + b[t + B - 1] : a[t + B - 1];
-      w[t - t0] = wrow[t < XR ? XR - t : t - XR];
+  for (int zi = 0; zi < ZB + kLatPlanes - 1; ++zi) {
+    // the next plane's fragments are read while this plane's products run
+    // (the barrier keeps the scheduler from reading every plane at once)
+    const half8 bh = nh, bl = nl;
+    if (zi + 1 < ZB + kLatPlanes - 1) {
+      nh = *reinterpret_cast<const half8*>(hi + (zi + 1) * plane);
+      nl = *reinterpret_cast<const half8*>(lo + (zi + 1) * plane);
     }
+    if (zi >= zlo && zi < zhi) {                       // (planes outside the grid are zero)
+      // product by product over the planes: dependent MFMAs stay apart
 #pragma unroll
-    for (int t = t0; t < t0 + 4 && t < NT; ++t)
+      for (int j = 0; j < kLatPlanes; ++j)
+        if (zi - j >= 0 && zi - j < ZB)
+          acc[zi - j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(al[j], bh, acc[zi - j], 0, 0, 0);
 #pragma unroll
-      for (int bb = 0; bb < B; ++bb) acc[bb] = fmaf(w[t - t0], v[bb + t], acc[bb]);
+      for (int j = 0; j < kLatPlanes; ++j)
+        if (zi - j >= 0 && zi - j < ZB)
+          acc[zi - j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[j], bl, acc[zi - j], 0, 0, 0);
+#pragma unroll
+      for (int j = 0; j < kLatPlanes; ++j)
+        if (zi - j >= 0 && zi - j < ZB)
+          acc[zi - j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[j], bh, acc[zi - j], 0, 0, 0);
+    }
     __builtin_amdgcn_sched_barrier(0);
   }
 }
 
-template <int B, bool PAIR>
-__device__ __forceinline__ void row_win_dispatch(int xr, float* acc, const float* a, const float* b,
-                                                 const float* w) {
-  switch (xr) {
-    case 0: row_win<B, 0, PAIR>(acc, a, b, w); break;
-    case 1: row_win<B, 1, PAIR>(acc, a, b, w); break;
-    case 2: row_win<B, 2, PAIR>(acc, a, b, w); break;
-    case 3: row_win<B, 3, PAIR>(acc, a, b, w); break;
-    case 4: row_win<B, 4, PAIR>(acc, a, b, w); break;
-    case 5: row_win<B, 5, PAIR>(acc, a, b, w); break;
-    case 6: row_win<B, 6, PAIR>(acc, a, b, w); break;
-    case 7: row_win<B, 7, PAIR>(acc, a, b, w); break;
-    case 8: row_win<B, 8, PAIR>(acc, a, b, w); break;
-    case 9: row_win<B, 9, PAIR>(acc, a, b, w); break;
-    case 10: row_win<B, 10, PAIR>(acc, a, b, w); break;
-    case 11: row_win<B, 11, PAIR>(acc, a, b, w); break;
-    case 12: row_win<B, 12, PAIR>(acc, a, b, w); break;
-    case 13: row_win<B, 13, PAIR>(acc, a, b, w); break;
-    case 14: row_win<B, 14, PAIR>(acc, a, b, w); break;
-    case 15: row_win<B, 15, PAIR>(acc, a, b, w); break;
-    default: row_win<B, 16, PAIR>(acc, a, b, w); break;
+// The same for the wings: the lower half-wave reads input plane zi, the upper
+// one plane zi + 1, so one fragment pair serves stencil planes 2p and 2p + 1.
+template <int ZB>
+__device__ __forceinline__ void lat_wing(floatx4* acc, const half8* wh, const half8* wl, const _Float16* hi,
+                                         const _Float16* lo, int plane, int zlo, int zhi) {
+  half8 nh = *reinterpret_cast<const half8*>(hi), nl = *reinterpret_cast<const half8*>(lo);
+#pragma unroll
+  for (int zi = 0; zi < ZB + 2; ++zi) {
+    const half8 bh = nh, bl = nl;
+    if (zi + 1 < ZB + 2) {
+      nh = *reinterpret_cast<const half8*>(hi + (zi + 1) * plane);
+      nl = *reinterpret_cast<const half8*>(lo + (zi + 1) * plane);
+    }
+    if (zi + 1 >= zlo && zi < zhi) {
+#pragma unroll
+      for (int p = 0; p < 2; ++p)
+        if (zi - 2 * p >= 0 && zi - 2 * p < ZB)
+          acc[zi - 2 * p] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wl[p], bh, acc[zi - 2 * p], 0, 0, 0);
+#pragma unroll
+      for (int p = 0; p < 2; ++p)
+        if (zi - 2 * p >= 0 && zi - 2 * p < ZB)
+          acc[zi - 2 * p] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wh[p], bl, acc[zi - 2 * p], 0, 0, 0);
+#pragma unroll
+      for (int p = 0; p < 2; ++p)
+        if (zi - 2 * p >= 0 && zi - 2 * p < ZB)
+          acc[zi - 2 * p] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wh[p], bh, acc[zi - 2 * p], 0, 0, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
   }
 }
 
-// part 0: the tiles of level 0; part 1: the tiles of levels 1 .. l-2 and the
-// top level; part 2: every tile and the top level.
-template <int B, int W>
-__global__ void __launch_bounds__(W * kWave, B <= 6 ? 8 : 4) k_lattice_win(KArgs A, int part) {
-  constexpr int kLatWaves = W, kLatThreads = W * kWave;
+// part 0: the tiles of level 0; part 1: the top level and the tiles of levels
+// 1 .. l-2; part 2: the top level and every tile.
+// ZS groups of 4 waves take ZB planes each of a block's window.
+template <int ZB, int ZS>
+__global__ void __launch_bounds__(ZS * 4 * kWave, 2) k_lattice_mfma(KArgs A, int part) {
+  constexpr int kLatWaves = 4 * ZS;
   int blk;
-  const SysDesc& S = sys_of(A, blk, false);
+  __shared__ __align__(16) SysDesc sdesc;
+  __shared__ int wmax[kLatWaves];
+  const SysDesc& S = stage_desc(sys_of(A, blk, false), &sdesc);
   const Geom& g = S.g;
   const LatLaunch& P = S.lat;
-  {
-    int first;
-    const int nl = lattice_tile_blocks(P, part, first);
-    if (blk >= nl) {                                    // a top-level block (no barriers)
-      top_node(S, (blk - nl) * kLatWaves + (int)(threadIdx.x / kWave), threadIdx.x & (kWave - 1));
-      return;
-    }
-    blk += first;
-  }
-  const int4* __restrict__ rows_g = S.d.rows_c;
-  const float* __restrict__ wc_g = S.d.weights_c;
-  const float* __restrict__ qgrid = S.d.qgrid;
-  float* __restrict__ ucut = S.d.ucut;
-  extern __shared__ float4 lds4[];
-  int4* rows = reinterpret_cast<int4*>(lds4);
-  float* wc = reinterpret_cast<float*>(lds4 + P.n_rows);
-  float* win = wc + P.n_wc;
-  int bid = blk, li = 0;
-  while (li + 1 < P.n && bid >= P.t[li + 1].block0) ++li;
-  const LatTile T = P.t[li];
-  const Level Lv = g.lv[T.level];
-  bid -= T.block0;
-  // block = (tile, row group); the group's rows have nz in [nz_lo, nz_hi]
-  const int G = T.groups;
-  const int grp = bid % G;
-  const int tile = bid / G;
-  const int r_lo = P.grp[G][grp], r_hi = P.grp[G][grp + 1];
-  const int nz_lo = r_lo < r_hi ? rows_g[r_lo].x : 0, nz_hi = r_lo < r_hi ? rows_g[r_hi - 1].x : 0;
-  const int bx = tile % T.ntx, by = (tile / T.ntx) % T.nty, bz = tile / (T.ntx * T.nty);
-  const int H = P.H;
-  const int x0 = bx * T.xl * B, y0 = by * T.ty, z0 = bz * T.tz;
-  // window: planes z0 + nz_lo .. z0 + tz - 1 + nz_hi, rows y0 - H .., columns x0 - H ..
-  const int WX = T.xl * B + 2 * H, PY = T.ty + 2 * H, WZ = T.tz + nz_hi - nz_lo, PX = T.px, PP = T.pp;
-  const float* qk = qgrid + Lv.off;
-  const int NX = Lv.n[0], NY = Lv.n[1], NZ = Lv.n[2];
-
-  for (int i = threadIdx.x; i < P.n_rows; i += kLatThreads) rows[i] = rows_g[i];
-  for (int i = threadIdx.x; i < P.n_wc; i += kLatThreads) wc[i] = wc_g[i];
-  // the window in runs of 4 consecutive x (index arithmetic and the y, z
-  // bounds once per run), 2 runs per thread at a time: 8 loads in flight
-  const int WXq = (WX + 3) >> 2;
-  const int nq = WZ * PY * WXq;                        // < 2^16 (bounded by the LDS budget)
-  const float inv_wq = 1.f / (float)WXq, inv_py = 1.f / (float)PY;
-  for (int i0 = 0; i0 < nq; i0 += 2 * kLatThreads) {
-    float v[2][4];
-    int dst[2], nx4[2];
-#pragma unroll
-    for (int u = 0; u < 2; ++u) {
-      const int i = i0 + u * kLatThreads + threadIdx.x;
-      dst[u] = -1;
-      nx4[u] = 0;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) v[u][e] = 0.f;
-      if (i < nq) {
-        int xq, yy;
-        const int zz = fdiv(fdiv(i, WXq, inv_wq, xq), PY, inv_py, yy);
-        const int xx = 4 * xq;
-        dst[u] = zz * PP + yy * PX + xx;
-        nx4[u] = min(4, WX - xx);
-        const int gx = x0 - H + xx, gy = y0 - H + yy, gz = z0 + nz_lo + zz;
-        if (gy >= 0 && gy < NY && gz >= 0 && gz < NZ) {
-          const float* src = qk + ((size_t)gz * NY + gy) * NX;
-#pragma unroll
-          for (int e = 0; e < 4; ++e)
-            if (e < nx4[u] && gx + e >= 0 && gx + e < NX) v[u][e] = src[gx + e];
-        }
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < 2; ++u)
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-        if (dst[u] >= 0 && e < nx4[u]) win[dst[u] + e] = v[u][e];
-  }
-  __syncthreads();
-
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  const int xi = lane % T.xl, yi = (lane / T.xl) % T.ty, zi = lane / (T.xl * T.ty);
-  const bool active = zi < T.tz;
-  const float* base = win + (zi - nz_lo) * PP + (yi + H) * PX + xi * B + H;
-  double tot[B];
-  float acc[B];
-#pragma unroll
-  for (int b = 0; b < B; ++b) {
-    tot[b] = 0.0;
-    acc[b] = 0.f;
+  auto uniform = [](int v) { return __builtin_amdgcn_readfirstlane(v); };
+  if (part != 0) {
+    // the top level's blocks first: they wait for memory more than they compute
+    const int nt = (uniform(g.lv[g.levels - 1].count) + kLatWaves - 1) / kLatWaves;
+    if (blk < nt) {
+      top_node(S, blk * kLatWaves + wave, lane);
+      return;
+    }
+    blk -= nt;
   }
-  int cnt = 0;
-  int4 row = (r_lo + wave < r_hi) ? rows[r_lo + wave] : make_int4(0, 0, 0, 0);
-  for (int r = r_lo + wave; r < r_hi; r += kLatWaves) {
-    const int4 cur = row;
-    if (r + kLatWaves < r_hi) row = rows[r + kLatWaves];           // next descriptor in flight
-    const int nz = __builtin_amdgcn_readfirstlane(cur.x);
-    const int ny = __builtin_amdgcn_readfirstlane(cur.y);
-    const int xr = __builtin_amdgcn_readfirstlane(cur.z);
-    const int wo = __builtin_amdgcn_readfirstlane(cur.w);
-    if (active) {
-      const float* a = base + nz * PP + ny * PX - xr;
-      if (ny == 0) {
-        row_win_dispatch<B, false>(xr, acc, a, a, wc + wo);
-      } else {
-        const float* b = base + nz * PP - ny * PX - xr;
-        row_win_dispatch<B, true>(xr, acc, a, b, wc + wo);
+  // block = (level, tile, phase group)
+  int li = 0;
+  if (part == 1) {
+    blk += P.t[1].block0;
+    li = 1;
+  }
+  while (li + 1 < P.n && blk >= P.t[li + 1].block0) ++li;
+  li = uniform(li);
+  const int bid = uniform(blk - P.t[li].block0), level = uniform(P.t[li].level);
+  const int ntx = uniform(P.t[li].ntx), nty = uniform(P.t[li].nty), G = uniform(P.t[li].groups);
+  const int H = uniform(P.H), H1 = H + 1, n2max = uniform(P.n2max), phases = uniform(P.phases);
+  const int NX = uniform(g.lv[level].n[0]), NY = uniform(g.lv[level].n[1]), NZ = uniform(g.lv[level].n[2]);
+  const int lv_off = uniform(g.lv[level].off);
+  const int tile = bid / G, grp = bid - tile * G;
+  const int bz = tile / (ntx * nty), by = (tile - bz * ntx * nty) / ntx, bx = tile - (bz * nty + by) * ntx;
+  // a periodic level's outputs are the nodes of one period (the ghost copies
+  // of u^k are filled afterwards), from the multiple of 8 below it along x, so
+  // that octets do not straddle the level's first node
+  const int ghost = uniform(g.periodic) ? uniform(g.ghost) : 0;
+  const int x0 = (ghost & ~7) + 16 * bx, y0 = ghost + 16 * by, z0 = ghost + ZB * ZS * bz;
+  const int XE = NX - ghost, YE = NY - ghost, ZE = NZ - ghost;          // end of the outputs
+  const float* qk = S.d.qgrid + lv_off;
+  const int WL = lat_left(H), noct = lat_octets(H), pitch = lat_pitch(H), rows = lat_rows(H);
+  const int plane = rows * pitch;
+  constexpr int NP = ZB * ZS + kLatPlanes - 1;          // input planes of a phase
+  extern __shared__ float4 lds4[];
+  _Float16* hi = reinterpret_cast<_Float16*>(lds4);
+  _Float16* lo = hi + NP * plane;
+  // staging: a thread takes one octet (8 x values) of one row, in planes sp .. sp + NPT - 1
+  constexpr int NPT = (NP + ZS - 1) / ZS;               // planes per thread
+  const int st = (int)threadIdx.x & 255, sp = NPT * uniform((int)threadIdx.x >> 8);
+  const int sr = st / noct, so = st - sr * noct;
+  const int sx = x0 + 8 * (so - WL), sy = y0 - H + sr;
+  const bool smine = sr < rows;
+  // (octets left of node 0 hold no node; past the row's end the next row's
+  // nodes are read and dropped)
+  const bool sok = smine && sy >= 0 && sy < NY && sx >= 0 && sx < NX;
+  const int skeep = NX - sx;                            // values of the octet that are nodes of the row
+  const float* ssrc = qk + (sok ? (size_t)sy * NX + sx : 0);
+  const int sdst = sr * pitch + 8 * so;
+  // fragment columns: lane & 15 the node row, lane / 16 the octet of inputs
+  const int col = lane & 15, quad = lane >> 4;
+  const int zs = wave >> 2, wk = wave & 3, zw = z0 + ZB * zs;
+  const int at = ZB * zs * plane + (H + col) * pitch;
+  const int main_at = at + 8 * (WL - 1 + quad);
+  const int wing_at = at + (quad >> 1) * plane + 40 * (quad & 1);
+  double tot[ZB][4];
+#pragma unroll
+  for (int z = 0; z < ZB; ++z)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) tot[z][r] = 0.0;
+  const uint4* __restrict__ frags = reinterpret_cast<const uint4*>((const void*)S.d.lat_frags) + lane;
+  constexpr int kFrag = kLatFragBytes / 16;
+  auto fragment = [&](int id, half8& fh, half8& fl) {
+    fh = __builtin_bit_cast(half8, frags[id * kFrag]);
+    fl = __builtin_bit_cast(half8, frags[id * kFrag + kWave]);
+  };
+  const int ph0 = phases * grp / G, ph1 = phases * (grp + 1) / G;
+  float4_a4 v[NPT][2];
+  auto load_planes = [&](int ph) {
+    const int first = z0 + kLatPlanes * ph - H + sp;
+#pragma unroll
+    for (int p = 0; p < NPT; ++p) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[p][e >> 2].v[e & 3] = 0.f;
+      if (first + p >= 0 && first + p < NZ && sok) {
+        const float* src = ssrc + (size_t)(first + p) * (NX * NY);
+        v[p][0] = *reinterpret_cast<const float4_a4*>(src);
+        v[p][1] = *reinterpret_cast<const float4_a4*>(src + 4);
       }
     }
-    if (++cnt == 4) {                                  // float32 groups of 4 rows, float64 total
+  };
+  load_planes(ph0);
+#pragma unroll 1
+  for (int ph = ph0; ph < ph1; ++ph) {
+    const int nz0 = kLatPlanes * ph - H;
+    if (z0 + nz0 + NP <= 0 || z0 + nz0 >= NZ) {         // no input plane lies in the grid
+      if (ph + 1 < ph1) load_planes(ph + 1);
+      continue;
+    }
+    const int zlo = max(0, -(zw + nz0)), zhi = NZ - (zw + nz0);   // the wave's input planes that do
+    // the wave's rows of the phase: row i stands for ny = 0 (i = 0), +(i + 1)/2
+    // (odd i) or -(i + 1)/2; the plan cuts them into shares of equal cost
+    const int i1 = uniform(P.cut[ph][wk + 1]);
+    int i = uniform(P.cut[ph][wk]);
+    // fragments of the wave's first row, on their way while the window is staged
+    half8 ah[kLatPlanes], al[kLatPlanes];
+    auto main_fragments = [&](int ay) {
 #pragma unroll
-      for (int b = 0; b < B; ++b) {
-        tot[b] += (double)acc[b];
-        acc[b] = 0.f;
+      for (int j = 0; j < kLatPlanes; ++j) fragment(abs(nz0 + j) * H1 + ay, ah[j], al[j]);
+    };
+    main_fragments((i + 1) >> 1);
+    if (__any(sok && skeep < 8)) {
+#pragma unroll
+      for (int p = 0; p < NPT; ++p)
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          if (e >= skeep) v[p][e >> 2].v[e & 3] = 0.f;
+    }
+    // inputs are taken times a power of two: the largest |q| of the window lands in [2^13, 2^14)
+    float vm = 0.f;
+#pragma unroll
+    for (int p = 0; p < NPT; ++p)
+#pragma unroll
+      for (int e = 0; e < 8; e += 2)
+        vm = fmaxf(vm, fmaxf(fabsf(v[p][e >> 2].v[e & 3]), fabsf(v[p][e >> 2].v[(e & 3) + 1])));
+    const int wm = wave_max_s(__float_as_int(vm));
+    __syncthreads();                                    // the previous phase is done with the window (and wmax)
+    if (lane == 0) wmax[wave] = wm;
+    __syncthreads();
+    int qbits = wmax[0];
+#pragma unroll
+    for (int w = 1; w < kLatWaves; ++w) qbits = max(qbits, wmax[w]);
+    const int sbits = min(254, max(1, 267 - ((uniform(qbits) >> 23) & 255)));
+    const float qscale = __int_as_float(sbits << 23);
+    if (smine) {
+#pragma unroll
+      for (int p = 0; p < NPT; ++p) {
+        if (sp + p >= NP) break;
+        half8 h, l;
+#pragma unroll
+        for (int e = 0; e < 8; e += 2) {
+          floatx2 x = {v[p][e >> 2].v[e & 3] * qscale, v[p][e >> 2].v[(e & 3) + 1] * qscale};
+          const half2v hh = __builtin_convertvector(x, half2v);
+          x = x - __builtin_convertvector(hh, floatx2);
+          const half2v ll = __builtin_convertvector(x, half2v);
+          h[e] = hh[0];
+          h[e + 1] = hh[1];
+          l[e] = ll[0];
+          l[e + 1] = ll[1];
+        }
+        *reinterpret_cast<half8*>(hi + (sp + p) * plane + sdst) = h;
+        *reinterpret_cast<half8*>(lo + (sp + p) * plane + sdst) = l;
       }
-      cnt = 0;
+    }
+    if (ph + 1 < ph1) load_planes(ph + 1);              // the next phase's inputs, on their way during this one's products
+    __syncthreads();
+    // undoes the scale of the inputs
+    const double unscale = __longlong_as_double((long long)(1023 + 127 - sbits) << 52);
+    // the plane of the phase nearest to the centre (the longest rows)
+    const int az = nz0 > 0 ? nz0 : max(0, -(nz0 + kLatPlanes - 1));
+#pragma unroll 1
+    while (i < i1) {
+      const int ay = (i + 1) >> 1;
+      // this wave's signs of the row pair, where some of the 16 input rows lie in the grid
+      const bool up = (i == 0 || (i & 1)) && y0 + ay < NY;
+      const bool down = i > 0 && (!(i & 1) || i + 1 < i1) && y0 + 15 - ay >= 0;
+      i += (i & 1) ? 2 : 1;
+      half8 wh[2], wl[2];
+      const bool wing = H > 8 && 81 + ay * ay + az * az <= n2max;
+      if (wing)
+#pragma unroll
+        for (int p = 0; p < 2; ++p) fragment((H + kLatPlanes + 2 * ph + p) * H1 + ay, wh[p], wl[p]);
+      floatx4 acc[ZB];
+#pragma unroll
+      for (int z = 0; z < ZB; ++z) acc[z] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+      for (int sgn = up ? 1 : -1; sgn >= (down ? -1 : 1); sgn -= 2) {
+        const int d = sgn * ay * pitch;
+        lat_row<ZB>(acc, ah, al, hi + main_at + d, lo + main_at + d, plane, zlo, zhi);
+        if (wing) lat_wing<ZB>(acc, wh, wl, hi + wing_at + d, lo + wing_at + d, plane, zlo, zhi);
+      }
+      if (i < i1) main_fragments((i + 1) >> 1);         // the next row's, on their way during the sums
+#pragma unroll
+      for (int z = 0; z < ZB; ++z)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) tot[z][r] = fma((double)acc[z][r], unscale, tot[z][r]);
     }
   }
-#pragma unroll
-  for (int b = 0; b < B; ++b) tot[b] += (double)acc[b];
-  __syncthreads();                                     // window no longer needed
+  // the waves' totals meet in LDS and are added in wave order, each wave taking
+  // its share of the (plane, output row) values: 4 ZB values per lane
   double* red = reinterpret_cast<double*>(lds4);
-#pragma unroll
-  for (int b = 0; b < B; ++b) red[((size_t)wave * kWave + lane) * B + b] = tot[b];
   __syncthreads();
-  // every thread sums one output over the waves (in wave order)
-  for (int o = threadIdx.x; o < kWave * B; o += kLatThreads) {
-    const int l = o / B, b = o - l * B;
-    const int lxi = l % T.xl, lyi = (l / T.xl) % T.ty, lzi = l / (T.xl * T.ty);
-    const int x = x0 + lxi * B + b, y = y0 + lyi, z = z0 + lzi;
-    if (lzi >= T.tz || x >= NX || y >= NY || z >= NZ) continue;
-    double r[kLatWaves];
 #pragma unroll
-    for (int w = 0; w < kLatWaves; ++w) r[w] = red[((size_t)w * kWave + l) * B + b];
-    double v = 0.0;
+  for (int z = 0; z < ZB; ++z)
 #pragma unroll
-    for (int w = 0; w < kLatWaves; ++w) v += r[w];
-    const size_t node = ((size_t)z * NY + y) * NX + x;
-    if (G == 1)
-      ucut[Lv.off + node] = (float)ldexp(v, -T.level);
-    else
-      S.d.lat_part[T.part0 + (size_t)grp * Lv.count + node] = v;
+    for (int r = 0; r < 4; ++r) red[((wave * ZB + z) * 4 + r) * kWave + lane] = tot[z][r];
+  __syncthreads();
+  // undo the scale of the weights; a tile in one block also the level's 2^-k
+  // (the consumers of partials apply it to their sum)
+  const double wscale = __longlong_as_double((long long)(1023 - uniform(P.wexp) - (G == 1 ? level : 0)) << 52);
+  float* __restrict__ ucut = S.d.ucut + lv_off;
+  double* __restrict__ out = S.d.lat_part + uniform(P.t[li].part0) + (size_t)grp * uniform(g.lv[level].count);
+  const int y = y0 + col;
+#pragma unroll
+  for (int k = 0; k < ZB; ++k) {
+    const int t = wk * ZB + k, z = t >> 2, r = t & 3;    // value t of the group's 4 ZB
+    double s = 0.0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) s += red[((4 * zs + w) * ZB * 4 + t) * kWave + lane];
+    s *= wscale;
+    const int x = x0 + 4 * quad + r;
+    if (zw + z < ZE && y < YE && x >= ghost && x < XE) {
+      const size_t node = ((size_t)(zw + z) * NY + y) * NX + x;
+      if (G == 1)
+        ucut[node] = (float)s;
+      else
+        out[node] = s;
+    }
   }
 }
 
 // u^{k,cut} at node `node` of level k (level-local index): the stored value,
-// or, where the level's lattice tiles were split into row groups, the sum of
+// or, where the level's lattice tiles were split into phase groups, the sum of
 // the groups' float64 partials in group order (with `store`, written back into
 // u^{k,cut} so the grid is complete after the prolongation).  The partials are
 // loaded together.
@@ -3220,7 +3312,7 @@ SysBlocks system_blocks(const Geom& g, const LatLaunch& lat, int n_partials) {
   const int top_nodes = g.lv[g.levels - 1].count;
   b.lattice_all = b.lattice0 + b.lattice;
   if (g.levels > 1 && lat.b > 0) {
-    const int tb = (top_nodes + lat.waves - 1) / lat.waves;  // top level rides in the coarse launch
+    const int w = lat_waves(lat.b), tb = (top_nodes + w - 1) / w;  // top level rides in the coarse launch
     b.lattice += tb;
     b.lattice_all += tb;
     b.top = 0;
@@ -3406,19 +3498,18 @@ hipError_t launch_eval(int mode, const LaunchGeom& L, hipStream_t s, const Io& i
     if (sg.blocks == 0) return;
     const KArgs A = args(sg);
     const int nb = sg.blocks;
-#define MSM_LAT(BB, WW)                                                                                      \
-  do {                                                                                                      \
-    (void)hipFuncSetAttribute((const void*)k_lattice_win<BB, WW>, hipFuncAttributeMaxDynamicSharedMemorySize, \
-                              L.lat_lds);                                                                   \
-    k_lattice_win<BB, WW><<<nb, WW * kWave, L.lat_lds, ls>>>(A, part);                                       \
+#define MSM_LAT(ZB, ZS)                                                                                        \
+  do {                                                                                                         \
+    (void)hipFuncSetAttribute((const void*)k_lattice_mfma<ZB, ZS>, hipFuncAttributeMaxDynamicSharedMemorySize, \
+                              L.lat_lds);                                                                      \
+    k_lattice_mfma<ZB, ZS><<<nb, ZS * 4 * kWave, L.lat_lds, ls>>>(A, part);                                    \
   } while (0)
-    const bool few = L.lat_waves == kLatWavesFew;
     if (L.lat_b == 4) {
-      if (few) MSM_LAT(4, kLatWavesFew); else MSM_LAT(4, kLatWavesMany);
+      MSM_LAT(4, 1);
     } else if (L.lat_b == 6) {
-      if (few) MSM_LAT(6, kLatWavesFew); else MSM_LAT(6, kLatWavesMany);
+      MSM_LAT(6, 1);
     } else if (L.lat_b == 8) {
-      if (few) MSM_LAT(8, kLatWavesFew); else MSM_LAT(8, kLatWavesMany);
+      MSM_LAT(4, 2);
     } else {
       k_lattice<<<nb, kBlock, 0, ls>>>(A, part);
     }

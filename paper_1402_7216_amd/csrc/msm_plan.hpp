@@ -24,19 +24,16 @@ struct msm_plan {
   msm_pair_params pp{};                      // parameters of a pair-method plan (g.pair != 0)
   Geom g;
   std::vector<msm::StencilRow> rows;         // full stencil rows (untiled lattice kernel)
-  std::vector<int4> rows_c;                  // compact rows of the windowed kernel
-  std::vector<float> weights_c;              // compact weights of the windowed kernel
+  std::vector<uint16_t> lat_frags;           // weight fragments of the tiled lattice kernel (float16 bits)
   std::vector<float> weights;                // full stencil weights
   std::vector<double> top;                   // FP64 top-level kernel table
   int n_partials = 1;
   int bin2_blocks = 0;                       // blocks of the two-kernel binning where it is possible
   bool prefer_bin2 = false;                  // two-kernel binning over one kernel where both work (batches)
-  int lat_waves = 0;                         // waves per lattice block: 0 by the level-0 tiles (batches: 16)
   int max_cells = 0;                         // link cells of the finest cell reach (sizes the cell sections)
   long long max_bin_hist = 0;                // two-kernel histogram entries of any cell reach
   msm::LatLaunch lat;
-  int lat_tables = 0;                        // LDS bytes of the compact stencil tables
-  int lat_part_max = 0;                      // lattice row-group partials of the largest tuning
+  int lat_part_max = 0;                      // lattice phase-group partials of the largest tuning
   int short_cap = 0;                         // short-range blocks (0: one per work item)
   int streams = 3;                           // stream layout of an evaluation (msm_tuning.streams)
   int short_after = 1;                       // start of the side-stream short range (msm_tuning.short_after)
@@ -94,9 +91,6 @@ msm_status batch_shape(const msm_batch* B, int32_t* n_sys, int32_t* total_atoms)
 // Apply tuning knobs (zero fields keep the current value).  Host-side only;
 // the caller re-uploads descriptors.
 void retune(msm_plan* P, const msm_tuning& t);
-// Waves per windowed lattice block for every later tile choice (0: by the
-// level-0 tile count); re-chooses the current tiles.  Host-side only.
-void set_lattice_waves(msm_plan* P, int waves);
 // Reject knob values outside their documented ranges.
 msm_status check_tuning(const msm_tuning* t);
 // Capture the work `launch` enqueues on a private stream into an instantiated graph.
