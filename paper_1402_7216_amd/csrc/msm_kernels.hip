@@ -1307,11 +1307,35 @@ __device__ __forceinline__ void row_window(const Geom& g, const int* start, int 
   hi = start[jrow + cell_x(g, pi.x + e) + 1];
 }
 
+// A copy of v in a vector register of its own, which the compiler cannot turn
+// back into the scalar it came from.
+__device__ __forceinline__ float in_vgpr(float v) {
+  float w;
+  asm volatile("v_mov_b32 %0, %1" : "=v"(w) : "s"(v));
+  return w;
+}
+
+// The constants of the pair terms, each in a vector register: an instruction
+// that reads a scalar register takes 4.6 cycles of its SIMD, one that reads
+// vector registers or inline constants 2.6 to 3.1.  With them, the distance
+// test and the walk in such instructions k_short takes 904 us instead of 940
+// at 1,000,000 atoms (order 6, a = 12) and 209 instead of 216 at 100,000 with
+// the Wolf function; it is bound by the vector instructions it issues (2.8
+// cycles each on average, 8 waves per SIMD).
+template <int M>
+struct PairConst {
+  float neg_tiny;              // -2^-149
+  float inv_a, inv_a2;         // 1/a, 1/a^2
+  float gc[M + 1];             // coefficients of gamma in t = (r/a)^2 - 1
+  float dc[M + 1];             // coefficients of gamma'(r/a)/(a^2 r) in r^2
+  float pk[4];                 // pair methods
+  float ec[kWolfTerms];        // Wolf
+};
+
 // Four staged j atoms against the lane's atom pi: the pair function of KIND
 // for each one with 0 < r^2 < a^2, added to the lane's sums.
 template <int M, bool FORCES, int KIND>
-__device__ __forceinline__ void short_pairs4(const float4* jp, const float4& pi, unsigned a2m1, float inv_a,
-                                             float inv_a2, const float* dc, const float* pk, const float* ec,
+__device__ __forceinline__ void short_pairs4(const float4* jp, const float4& pi, unsigned a2, const PairConst<M>& K,
                                              float& ax, float& ay, float& az, float& ap) {
   float4 pj[4];
 #pragma unroll
@@ -1319,10 +1343,11 @@ __device__ __forceinline__ void short_pairs4(const float4* jp, const float4& pi,
 #pragma unroll
   for (int v = 0; v < 4; ++v) {
     const float dx = pi.x - pj[v].x, dy = pi.y - pj[v].y, dz = pi.z - pj[v].z;
-    const float r2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
-    // one predicate (non-short-circuit), so a single branch per pair
-    // 0 < r2 < a2 as one unsigned compare of the bit patterns (r2 >= +0)
-    if (__float_as_uint(r2) - 1u < a2m1) {
+    // the smallest float taken off the sum: it turns a distance of zero
+    // negative, whose bit pattern is a large unsigned, and rounds away in any
+    // other; so 0 < r2 < a2 is one unsigned compare (and one branch per pair)
+    const float r2 = fmaf(dx, dx, fmaf(dy, dy, fmaf(dz, dz, K.neg_tiny)));
+    if (__float_as_uint(r2) < a2) {
       // hardware reciprocal square root plus one Newton step (the raw
       // instruction's error is biased, which would bias the energy)
       float ri = __builtin_amdgcn_rsqf(r2);
@@ -1335,15 +1360,15 @@ __device__ __forceinline__ void short_pairs4(const float4* jp, const float4& pi,
         // (Horner in r^2 with the rounded coefficients c_k / a^{2k+1}
         // leaves a fixed bias in every pair that does not average out
         // over the pairs of rigid molecules.)
-        const float t = fmaf(r2, inv_a2, -1.f);
-        float gm = binom_half(M);
+        const float t = fmaf(r2, K.inv_a2, -1.f);
+        float gm = K.gc[M];
 #pragma unroll
-        for (int k = M - 1; k >= 0; --k) gm = fmaf(gm, t, binom_half(k));
-        ap = fmaf(qj, fmaf(-gm, inv_a, ri), ap);
+        for (int k = M - 1; k >= 0; --k) gm = fmaf(gm, t, K.gc[k]);
+        ap = fmaf(qj, fmaf(-gm, K.inv_a, ri), ap);
         // gamma'(r/a)/(a^2 r) as a polynomial in r^2
-        float dg = dc[M];
+        float dg = K.dc[M];
 #pragma unroll
-        for (int k = M - 1; k >= 1; --k) dg = fmaf(dg, r2, dc[k]);
+        for (int k = M - 1; k >= 1; --k) dg = fmaf(dg, r2, K.dc[k]);
         if (FORCES) {
           const float wq = qj * fmaf(ri, ri * ri, dg);  // q_j (-g*'(r)/r)
           ax = fmaf(wq, dx, ax);
@@ -1356,13 +1381,13 @@ __device__ __forceinline__ void short_pairs4(const float4* jp, const float4& pi,
           e = ri;
           fr = ri * ri * ri;
         } else if (KIND == kPairShiftedForce) {
-          e = ri + fmaf(r2 * ri, pk[1], -2.f * pk[0]);
-          fr = ri * fmaf(ri, ri, -pk[1]);
+          e = ri + fmaf(r2 * ri, K.pk[1], -2.f * K.pk[0]);
+          fr = ri * fmaf(ri, ri, -K.pk[1]);
         } else {
-          const float ex = __builtin_amdgcn_exp2f(pk[3] * r2);
-          const float er = wolf_erfc(ec, pk[0] * (r2 * ri), ex);
-          e = fmaf(er, ri, -pk[1]);
-          fr = ri * ri * fmaf(er, ri, pk[2] * ex);
+          const float ex = __builtin_amdgcn_exp2f(K.pk[3] * r2);
+          const float er = wolf_erfc(K.ec, K.pk[0] * (r2 * ri), ex);
+          e = fmaf(er, ri, -K.pk[1]);
+          fr = ri * ri * fmaf(er, ri, K.pk[2] * ex);
         }
         ap = fmaf(qj, e, ap);
         if (FORCES) {
@@ -1378,8 +1403,10 @@ __device__ __forceinline__ void short_pairs4(const float4* jp, const float4& pi,
 
 template <int M, bool FORCES, int KIND, bool PER>
 // Eight 4-wave blocks per CU (LDS 20 KB each): 8 waves per SIMD, so at most 64
-// registers per lane.
-__global__ void __launch_bounds__(kShortThreads, 8) k_short(KArgs A, int lo_pm, int hi_pm) {
+// registers per lane.  The Wolf function holds its 11 coefficients too: seven
+// waves and 72 registers (225 us at 100,000 atoms, whole evaluation; 231 with
+// eight waves and the coefficients in scalar registers).
+__global__ void __launch_bounds__(kShortThreads, KIND == kPairWolf ? 7 : 8) k_short(KArgs A, int lo_pm, int hi_pm) {
   int blk;
   const SysDesc& S = sys_of(A, blk);
   const Geom& g = S.g;
@@ -1395,35 +1422,30 @@ __global__ void __launch_bounds__(kShortThreads, 8) k_short(KArgs A, int lo_pm, 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const int n_items = g.row_items * g.nc[1] * g.nc[2];
   const float a2 = g.a2, aw = g.a_win;
-  const unsigned a2m1 = __float_as_uint(a2) - 1u;
+  const unsigned a2b = __float_as_uint(a2);
   // Constants of the pair terms, copied into registers once: left to the
   // compiler they are reloaded from the descriptor inside the pair loop (a
-  // global load and wait per pair).  The force polynomial's coefficients go to
-  // vector registers (its first FMA would otherwise read two scalars), 1/a and
-  // 1/a^2 to scalar registers.
-  float dc[M + 1];
+  // global load and wait per pair).  0.5 and 1 stay inline constants.
+  PairConst<M> K;
+  K.neg_tiny = in_vgpr(-1.401298464324817e-45f);
+  if (KIND == kPairMsm) {
+    K.inv_a = M < 7 ? in_vgpr(g.inv_a) : __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(g.inv_a)));
+    K.inv_a2 = in_vgpr(g.inv_a2f);
 #pragma unroll
-  for (int k = 0; k <= M; ++k) {
-    float v;
-    asm volatile("v_mov_b32 %0, %1" : "=v"(v) : "s"(g.dr[k]));
-    dc[k] = v;
-  }
-  const float inv_a = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(g.inv_a)));
-  const float inv_a2 = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(g.inv_a2f)));
-  float pk[4];
+    for (int k = 0; k <= M; ++k) {
+      K.gc[k] = k < 2 || M > 4 ? binom_half(k) : in_vgpr(binom_half(k));
+      K.dc[k] = in_vgpr(g.dr[k]);
+    }
+  } else {
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    float v;
-    asm volatile("v_mov_b32 %0, %1" : "=v"(v) : "s"(g.pk[k]));
-    pk[k] = v;
+    for (int k = 0; k < 4; ++k) K.pk[k] = in_vgpr(g.pk[k]);
   }
-  float ec[kWolfTerms];
   if (KIND == kPairWolf) {
 #pragma unroll
-    for (int k = 0; k < kWolfTerms; ++k)
-      ec[k] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(g.ec[k])));
+    for (int k = 0; k < kWolfTerms; ++k) K.ec[k] = in_vgpr(g.ec[k]);
   }
   float4* jb = jbuf[wave];
+  const unsigned base = (unsigned)wave * sizeof(jbuf[0]);   // byte offset of jb in the block's buffer
   const int R = g.reach;
   // coincident atoms: the one- and two-kernel binnings leave them to this
   // pass, and so does every periodic plan (atoms one box edge apart coincide
@@ -1482,9 +1504,17 @@ __global__ void __launch_bounds__(kShortThreads, 8) k_short(KArgs A, int lo_pm, 
             const int a0B = LA + 4 + (nB > 0 ? loB - uB0 : 0);
             const int c4A = (nA + 3) & ~3;
             const int T = wave_max_s(c4A + nB);
+            // the walk in bytes of the block's buffer: past the A window
+            // (left < 0) the jump to the B window is added by a mask
+            const unsigned jump = (unsigned)(a0B - a0A - c4A) * sizeof(float4);
+            const unsigned last = base + (unsigned)E * sizeof(float4);
+            unsigned p = base + (unsigned)a0A * sizeof(float4);
+            int left = c4A - 1;
             for (int t0 = 0; t0 < T; t0 += 4) {
-              const int idx = t0 < c4A ? a0A + t0 : min(a0B + (t0 - c4A), E);
-              short_pairs4<M, FORCES, KIND>(jb + idx, pi, a2m1, inv_a, inv_a2, dc, pk, ec, ax, ay, az, ap);
+              const unsigned at = min(p + (jump & (unsigned)(left >> 31)), last);
+              short_pairs4<M, FORCES, KIND>((const float4*)((const char*)&jbuf[0][0] + at), pi, a2b, K, ax, ay, az, ap);
+              p += 4 * sizeof(float4);
+              left -= 4;
             }
             continue;
           }
@@ -1565,8 +1595,13 @@ __global__ void __launch_bounds__(kShortThreads, 8) k_short(KArgs A, int lo_pm, 
             }
             coincident |= zeros > ((i >= s0 + a0 && i < s0 + b0) ? 1 : 0);
           }
-          for (int t0 = 0; t0 < nmax; t0 += 4)
-            short_pairs4<M, FORCES, KIND>(jb + min(a0 + t0, kShortSeg), pi, a2m1, inv_a, inv_a2, dc, pk, ec, ax, ay, az, ap);
+          const unsigned last = base + kShortSeg * sizeof(float4);
+          unsigned p = base + (unsigned)a0 * sizeof(float4);
+          for (int t0 = 0; t0 < nmax; t0 += 4) {
+            short_pairs4<M, FORCES, KIND>((const float4*)((const char*)&jbuf[0][0] + min(p, last)), pi, a2b, K, ax, ay,
+                                          az, ap);
+            p += 4 * sizeof(float4);
+          }
         }
         }
         }
