@@ -1333,8 +1333,9 @@ struct PairConst {
 };
 
 // Four staged j atoms against the lane's atom pi: the pair function of KIND
-// for each one with 0 < r^2 < a^2, added to the lane's sums.
-template <int M, bool FORCES, int KIND>
+// for each one with 0 < r^2 < a^2, added to the lane's sums: the forces
+// (FORCES) and the potential (POT).
+template <int M, bool FORCES, bool POT, int KIND>
 __device__ __forceinline__ void short_pairs4(const float4* jp, const float4& pi, unsigned a2, const PairConst<M>& K,
                                              float& ax, float& ay, float& az, float& ap) {
   float4 pj[4];
@@ -1360,11 +1361,13 @@ __device__ __forceinline__ void short_pairs4(const float4* jp, const float4& pi,
         // (Horner in r^2 with the rounded coefficients c_k / a^{2k+1}
         // leaves a fixed bias in every pair that does not average out
         // over the pairs of rigid molecules.)
-        const float t = fmaf(r2, K.inv_a2, -1.f);
-        float gm = K.gc[M];
+        if (POT) {
+          const float t = fmaf(r2, K.inv_a2, -1.f);
+          float gm = K.gc[M];
 #pragma unroll
-        for (int k = M - 1; k >= 0; --k) gm = fmaf(gm, t, K.gc[k]);
-        ap = fmaf(qj, fmaf(-gm, K.inv_a, ri), ap);
+          for (int k = M - 1; k >= 0; --k) gm = fmaf(gm, t, K.gc[k]);
+          ap = fmaf(qj, fmaf(-gm, K.inv_a, ri), ap);
+        }
         // gamma'(r/a)/(a^2 r) as a polynomial in r^2
         float dg = K.dc[M];
 #pragma unroll
@@ -1401,7 +1404,7 @@ __device__ __forceinline__ void short_pairs4(const float4* jp, const float4& pi,
   }
 }
 
-template <int M, bool FORCES, int KIND, bool PER>
+template <int M, bool FORCES, bool POT, int KIND, bool PER>
 // Eight 4-wave blocks per CU (LDS 20 KB each): 8 waves per SIMD, so at most 64
 // registers per lane.  The Wolf function holds its 11 coefficients too: seven
 // waves and 72 registers (225 us at 100,000 atoms, whole evaluation; 231 with
@@ -1429,11 +1432,11 @@ __global__ void __launch_bounds__(kShortThreads, KIND == kPairWolf ? 7 : 8) k_sh
   PairConst<M> K;
   K.neg_tiny = in_vgpr(-1.401298464324817e-45f);
   if (KIND == kPairMsm) {
-    K.inv_a = M < 7 ? in_vgpr(g.inv_a) : __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(g.inv_a)));
-    K.inv_a2 = in_vgpr(g.inv_a2f);
+    if (POT) K.inv_a = M < 7 ? in_vgpr(g.inv_a) : __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(g.inv_a)));
+    if (POT) K.inv_a2 = in_vgpr(g.inv_a2f);
 #pragma unroll
     for (int k = 0; k <= M; ++k) {
-      K.gc[k] = k < 2 || M > 4 ? binom_half(k) : in_vgpr(binom_half(k));
+      if (POT) K.gc[k] = k < 2 || M > 4 ? binom_half(k) : in_vgpr(binom_half(k));
       K.dc[k] = in_vgpr(g.dr[k]);
     }
   } else {
@@ -1512,7 +1515,7 @@ __global__ void __launch_bounds__(kShortThreads, KIND == kPairWolf ? 7 : 8) k_sh
             int left = c4A - 1;
             for (int t0 = 0; t0 < T; t0 += 4) {
               const unsigned at = min(p + (jump & (unsigned)(left >> 31)), last);
-              short_pairs4<M, FORCES, KIND>((const float4*)((const char*)&jbuf[0][0] + at), pi, a2b, K, ax, ay, az, ap);
+              short_pairs4<M, FORCES, POT, KIND>((const float4*)((const char*)&jbuf[0][0] + at), pi, a2b, K, ax, ay, az, ap);
               p += 4 * sizeof(float4);
               left -= 4;
             }
@@ -1598,7 +1601,7 @@ __global__ void __launch_bounds__(kShortThreads, KIND == kPairWolf ? 7 : 8) k_sh
           const unsigned last = base + kShortSeg * sizeof(float4);
           unsigned p = base + (unsigned)a0 * sizeof(float4);
           for (int t0 = 0; t0 < nmax; t0 += 4) {
-            short_pairs4<M, FORCES, KIND>((const float4*)((const char*)&jbuf[0][0] + min(p, last)), pi, a2b, K, ax, ay,
+            short_pairs4<M, FORCES, POT, KIND>((const float4*)((const char*)&jbuf[0][0] + min(p, last)), pi, a2b, K, ax, ay,
                                           az, ap);
             p += 4 * sizeof(float4);
           }
@@ -3454,26 +3457,33 @@ hipError_t launch_eval(int mode, const LaunchGeom& L, hipStream_t s, const Io& i
     beg(slot, ss);
     const KArgs A = args(L.shortr);
     const int nb = L.shortr.blocks;
-#define MSM_SHORT_P(MM, FF, KK)                                                        \
-  do {                                                                                 \
-    if (L.short_periodic)                                                              \
-      k_short<MM, FF, KK, true><<<nb, kShortThreads, 0, ss>>>(A, lo_pm, hi_pm);         \
-    else                                                                               \
-      k_short<MM, FF, KK, false><<<nb, kShortThreads, 0, ss>>>(A, lo_pm, hi_pm);        \
+    // Nobody reads the potential of an evaluation that returns neither
+    // potentials nor an energy (the steps of a trajectory, an energy gradient
+    // without dE/dq): those pairs sum forces alone (three velocity Verlet
+    // steps of 50,000 atoms: 636 us; 664 with the potential).
+    const bool pot = mode == kModeEnergy || io.phi != nullptr || io.energy != nullptr;
+#define MSM_SHORT_P(MM, FF, PP, KK)                                                     \
+  do {                                                                                  \
+    if (L.short_periodic)                                                               \
+      k_short<MM, FF, PP, KK, true><<<nb, kShortThreads, 0, ss>>>(A, lo_pm, hi_pm);      \
+    else                                                                                \
+      k_short<MM, FF, PP, KK, false><<<nb, kShortThreads, 0, ss>>>(A, lo_pm, hi_pm);     \
   } while (0)
 #define MSM_SHORT(MM)                                                          \
   do {                                                                         \
-    if (forces)                                                                \
-      MSM_SHORT_P(MM, true, kPairMsm);                                         \
+    if (!forces)                                                               \
+      MSM_SHORT_P(MM, false, true, kPairMsm);                                  \
+    else if (pot)                                                              \
+      MSM_SHORT_P(MM, true, true, kPairMsm);                                   \
     else                                                                       \
-      MSM_SHORT_P(MM, false, kPairMsm);                                        \
+      MSM_SHORT_P(MM, true, false, kPairMsm);                                  \
   } while (0)
     if (L.pair == kPairCutoff)
-      MSM_SHORT_P(1, true, kPairCutoff);
+      MSM_SHORT_P(1, true, true, kPairCutoff);
     else if (L.pair == kPairShiftedForce)
-      MSM_SHORT_P(1, true, kPairShiftedForce);
+      MSM_SHORT_P(1, true, true, kPairShiftedForce);
     else if (L.pair == kPairWolf)
-      MSM_SHORT_P(1, true, kPairWolf);
+      MSM_SHORT_P(1, true, true, kPairWolf);
     else
     switch (L.m) {
       case 1: MSM_SHORT(1); break;
