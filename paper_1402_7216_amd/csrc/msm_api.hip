@@ -462,6 +462,8 @@ void refresh_launch(msm_plan* P) {
   lg.short_periodic = g.periodic != 0;
   for (int k = 0; k < g.levels; ++k) lg.ghost_blocks[k] = lg.periodic ? (g.lv[k].count + 255) / 256 : 0;
   lg.shortr.blocks = sb.shortr;
+  lg.short_parts = g.short_parts;
+  lg.short_split_rows = g.short_parts > 1;
   lg.anterp.blocks = sb.anterp;
   lg.lattice0.blocks = sb.lattice0;
   lg.lattice.blocks = sb.lattice;
@@ -537,11 +539,21 @@ void assign_short_rows(Geom& g) {
 // a row has row_items work items, item k taking chunks k, k + row_items, ...
 // (sized for the row's expected atom count, so each item gets about
 // item_chunks chunks; longer rows are still covered).
-void set_row_items(Geom& g, int item_chunks) {
+void set_row_items(Geom& g, int item_chunks, bool in_batch) {
   g.item_chunks = std::max(1, item_chunks);
   const double per_row = (double)g.n_atoms / ((double)g.nc[1] * g.nc[2]);
   const int chunks = std::max(1, (int)std::ceil(per_row / 64.0));
   g.row_items = std::max(1, (chunks + g.item_chunks - 1) / g.item_chunks);
+  const int rows = g.nc[1] * g.nc[2];
+  // a launch of at most one block per CU leaves the chip idle and lasts as long
+  // as one wave's rows: 16 waves per item instead of 4, each wave's rows in
+  // four parts (1,000 atoms in a cluster: k_short 45 -> 21 us, 9,000 periodic:
+  // 70 -> 35; at 24,000 atoms and 400 items it still gains, 53 -> 33, but there
+  // the grid stages beside it decide the time of an evaluation)
+  g.short_parts = g.row_items * rows <= msm::kShortSmallItems ? msm::kShortParts : 1;
+  // rows of an uneven cluster may be several times longer than the mean: a
+  // small system on its own has blocks to spare for them
+  if (g.short_parts > 1 && !in_batch) g.row_items = std::min(4 * g.row_items, std::max(g.row_items, msm::kShortSmallItems / rows));
 }
 
 void set_short_blocks(Geom& g, int cap) {
@@ -590,13 +602,13 @@ void set_cell_geometry(msm_plan* P, int reach) {
   P->bin2_blocks = (n_atoms > 0 && g.n_cells <= msm::kBinMaxCells && nb * g.n_cells <= msm::kBinMaxHist)
                        ? (int)nb : 0;
   const bool one = n_atoms > 0 && n_atoms <= msm::kBinRowAtoms && own <= msm::kBinRowCells;
-  g.bin_row_blocks = (one && !(P->prefer_bin2 && P->bin2_blocks > 0)) ? nbr : 0;
+  g.bin_row_blocks = (one && !(P->in_batch && P->bin2_blocks > 0)) ? nbr : 0;
   g.bin_blocks = g.bin_row_blocks == 0 ? P->bin2_blocks : 0;
   // otherwise by cell row first, then within each row, when the rows fit the
   // row binning's LDS histograms (else four kernels over the cells)
   const bool by_rows = n_atoms > 0 && g.bin_row_blocks == 0 && g.bin_blocks == 0 && rows <= msm::kBinRowsMax;
   g.binr_blocks = by_rows ? (int)((n_atoms + msm::kBinRChunk - 1) / msm::kBinRChunk) : 0;
-  set_row_items(g, g.item_chunks);
+  set_row_items(g, g.item_chunks, P->in_batch);
   set_short_blocks(g, P->short_cap);
 }
 
@@ -612,7 +624,7 @@ void retune(msm_plan* P, const msm_tuning& t) {
   if (t.lattice_b && P->lat.b && t.lattice_b != P->lat.b)
     choose_lattice_tiles(P->g, P->lat.H, P->lat, t.lattice_b);
   Geom& g = P->g;
-  if (t.item_chunks > 0) set_row_items(g, t.item_chunks);
+  if (t.item_chunks > 0) set_row_items(g, t.item_chunks, P->in_batch);
   if (t.short_blocks != 0) P->short_cap = t.short_blocks < 0 ? 0 : t.short_blocks;
   if (t.streams != 0) P->streams = t.streams;
   if (t.short_after != 0) P->short_after = t.short_after;
@@ -1125,6 +1137,7 @@ msm_status msm_plan_describe(const msm_plan* P, char* buf, size_t buf_bytes) {
        ", \"bin_row_blocks\": " + std::to_string(g.bin_row_blocks) + ", \"binr_blocks\": " +
        std::to_string(g.binr_blocks) +
        ", \"item_chunks\": " + std::to_string(g.item_chunks) + ", \"short_blocks\": " + std::to_string(g.short_blocks) +
+       ", \"short_parts\": " + std::to_string(g.short_parts) +
        ", \"streams\": " + std::to_string(P->streams) + ", \"short_after\": " + std::to_string(P->short_after) +
        ", \"short_split\": " + std::to_string(P->short_split);
   o += ", \"taps\": " + std::to_string(P->weights.size()) + ", \"halo\": " + std::to_string(P->lat.H);

@@ -135,6 +135,13 @@ void rebuild_maps(msm_batch* Bt) {
     }
   }
   for (int st = 0; st < kNumStages; ++st) stage_of(L, st)->blocks = (int)Bt->map[st].size();
+  // blocks of more waves where the whole batch still is a small launch of
+  // systems that split their rows; else a wave takes all parts of its rows
+  L.short_parts = L.shortr.blocks <= 2 * msm::kShortSmallItems ? msm::kShortParts : 1;
+  for (const msm_plan* P : Bt->plans) {
+    L.short_parts = std::min(L.short_parts, P->g.short_parts);
+    L.short_split_rows |= P->g.short_parts > 1;
+  }
 }
 
 void point_into(msm_batch* Bt, void* ws, msm::LaunchGeom& L) {
@@ -239,7 +246,7 @@ msm_status msm_batch_create(const msm_params* params, const int32_t* n_atoms, in
   // pays for a single system's latency but not when many systems fill the GPU
   if (n_sys > 1)
     for (msm_plan* P : Bt->plans) {
-      P->prefer_bin2 = true;
+      P->in_batch = true;
       set_cell_geometry(P, P->g.reach);
       refresh_launch(P);
     }

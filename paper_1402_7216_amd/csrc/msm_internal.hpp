@@ -13,6 +13,8 @@ namespace msm {
 
 constexpr int kMaxLevels = 12;
 constexpr int kShortWaves = 4;           // waves of a short-range block (they split the neighbour rows)
+constexpr int kShortParts = 4;           // parts a small system sums a wave's rows in, side by side in blocks of 16 waves
+constexpr int kShortSmallItems = 256;    // short-range work items up to which a system is small (one block per CU)
 constexpr int kShortRowsPerWave = 24;    // neighbour rows one wave can take
 constexpr int kMaxOrder = 6;
 constexpr int kMaxTopNodes = 1 << 17;     // all-pairs FP64 top level stays below ~1e10 pair terms
@@ -83,6 +85,8 @@ struct Geom {
                                                            // (its mirror (-oy, -oz)), 0xff: none
   int item_chunks;                 // short-range 64-atom chunks of a cell row per work item
   int row_items;                   // short-range work items per cell row (chunks interleaved)
+  int short_parts;                 // parts a wave's rows are summed in (1 or kShortParts): a function of the work items, so
+                                   // that a system's sums do not depend on the launch it is part of
   int short_blocks;                // blocks of the short-range launch (work items strided over them)
   // short-range constants
   float a2;                        // cutoff^2
@@ -325,6 +329,8 @@ struct LaunchGeom {
                                      // 3: the coarse lattice cutoff
   int short_split = 1000;            // per mille of its work items started there (the rest after the
                                      // lattice cutoff)
+  int short_parts = 1;               // row parts side by side: short-range blocks of 4 short_parts waves
+  bool short_split_rows = false;     // some system sums its rows in parts
   StageGrid zero, atoms, one, shortr, anterp, top, energy;
   StageGrid scan;                    // tiles of the four-kernel binning's cell-count scan
   StageGrid agather;                 // level-0 nodes (gather of the anterpolation partials)

@@ -1197,6 +1197,8 @@ __global__ void __launch_bounds__(kBRSThreads) k_binr_sort(KArgs A) {
 constexpr int kShortThreads = kShortWaves * kWave;
 constexpr int kShortSeg = 256;                   // j atoms a wave stages at a time (one row)
 constexpr int kShortBuf = 312;                   // entries of a wave's staging buffer (a row pair; 4 waves x 312 x 16 B: 8 blocks per CU)
+constexpr int kShortSegSplit = 192;              // the same for a system whose rows are split in parts
+static_assert(kShortBuf - kWave >= kShortSegSplit + 4 && kShortSegSplit % kWave == 0, "split staging sizes");
 static_assert(kShortBuf >= kShortSeg + 4 && kShortSeg % kWave == 0, "short-range staging sizes");
 
 __device__ __forceinline__ int cell_x(const Geom& g, float x) {
@@ -1404,12 +1406,17 @@ __device__ __forceinline__ void short_pairs4(const float4* jp, const float4& pi,
   }
 }
 
-template <int M, bool FORCES, bool POT, int KIND, bool PER>
+template <int M, bool FORCES, bool POT, int KIND, bool PER, bool SPLIT>
+// SPLIT: systems of few work items, whose rows each wave sums in g.short_parts
+// parts.  A block of 16 waves takes the four parts side by side; in a batch too
+// large for that a block of 4 waves takes them in turn, with the same sums in
+// the same order (0.6% of a batch of 64 systems).
 // Eight 4-wave blocks per CU (LDS 20 KB each): 8 waves per SIMD, so at most 64
 // registers per lane.  The Wolf function holds its 11 coefficients too: seven
 // waves and 72 registers (225 us at 100,000 atoms, whole evaluation; 231 with
-// eight waves and the coefficients in scalar registers).
-__global__ void __launch_bounds__(kShortThreads, KIND == kPairWolf ? 7 : 8) k_short(KArgs A, int lo_pm, int hi_pm) {
+// eight waves and the coefficients in scalar registers); a small periodic
+// system has one 16-wave block per CU, four waves per SIMD.
+__global__ void __launch_bounds__((SPLIT ? kShortParts : 1) * kShortThreads, SPLIT && PER ? 4 : (KIND == kPairWolf ? 7 : 8)) k_short(KArgs A, int lo_pm, int hi_pm) {
   int blk;
   const SysDesc& S = sys_of(A, blk);
   const Geom& g = S.g;
@@ -1420,9 +1427,20 @@ __global__ void __launch_bounds__(kShortThreads, KIND == kPairWolf ? 7 : 8) k_sh
   // far-away uncharged entries after each row: a lane reads 4 entries at a
   // time, and every entry past its window fails the cutoff test (same-row
   // atoms beyond the window lie farther than a)
-  __shared__ float4 jbuf[kShortWaves][kShortBuf];
+  extern __shared__ float4 jsplit[];                 // SPLIT: [waves of the block][kShortBuf]
+  __shared__ float4 jwhole[SPLIT ? 1 : kShortWaves * kShortBuf];
+  float4* jbuf = SPLIT ? jsplit : jwhole;
   const int lane = threadIdx.x & (kWave - 1);
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int slot = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const int wave = SPLIT ? slot % kShortWaves : slot;            // the wave's list of neighbour rows
+  const int parts = SPLIT ? g.short_parts : 1;
+  const int part0 = SPLIT ? slot / kShortWaves : 0;              // its first part of that list
+  const int part_step = SPLIT ? (int)blockDim.x / kShortThreads : 1;
+  // a split system's wave keeps the sums of its parts done at the end of its
+  // buffer: shorter row pairs and segments are staged (by the system's own
+  // split, so that its sums do not depend on the launch)
+  const int buf = SPLIT && parts > 1 ? kShortBuf - kWave : kShortBuf;
+  const int seg = SPLIT && parts > 1 ? kShortSegSplit : kShortSeg;
   const int n_items = g.row_items * g.nc[1] * g.nc[2];
   const float a2 = g.a2, aw = g.a_win;
   const unsigned a2b = __float_as_uint(a2);
@@ -1447,8 +1465,8 @@ __global__ void __launch_bounds__(kShortThreads, KIND == kPairWolf ? 7 : 8) k_sh
 #pragma unroll
     for (int k = 0; k < kWolfTerms; ++k) K.ec[k] = in_vgpr(g.ec[k]);
   }
-  float4* jb = jbuf[wave];
-  const unsigned base = (unsigned)wave * sizeof(jbuf[0]);   // byte offset of jb in the block's buffer
+  float4* jb = jbuf + slot * kShortBuf;
+  const unsigned base = (unsigned)(slot * kShortBuf) * sizeof(float4);   // byte offset of jb in the block's buffer
   const int R = g.reach;
   // coincident atoms: the one- and two-kernel binnings leave them to this
   // pass, and so does every periodic plan (atoms one box edge apart coincide
@@ -1473,7 +1491,8 @@ __global__ void __launch_bounds__(kShortThreads, KIND == kPairWolf ? 7 : 8) k_sh
       // ap: sum q_j g*(r) (MSM) or sum q_j e(r) (pair methods)
       float ax = 0.f, ay = 0.f, az = 0.f, ap = 0.f;
       bool coincident = false;
-      for (int q = 0; q < kShortRowsPerWave; ++q) {
+      for (int part = part0; part < parts; part += part_step) {
+      for (int q = part; q < kShortRowsPerWave; q += parts) {
         const int r0 = g.short_rows[wave][q];
         if (r0 == 0xff) break;
         const int r1 = g.short_pair[wave][q];
@@ -1490,7 +1509,7 @@ __global__ void __launch_bounds__(kShortThreads, KIND == kPairWolf ? 7 : 8) k_sh
           const int uA0 = wave_min_s(loA), uA1 = wave_max_s(hiA);
           const int uB0 = wave_min_s(loB), uB1 = wave_max_s(hiB);
           const int LA = max(uA1 - uA0, 0), LB = max(uB1 - uB0, 0);
-          if (LA + LB + 8 <= kShortBuf) {
+          if (LA + LB + 8 <= buf) {
             const int E = LA + 4 + LB;
 #pragma unroll
             for (int v = 0; v < (kShortBuf + kWave - 1) / kWave; ++v) {
@@ -1515,7 +1534,7 @@ __global__ void __launch_bounds__(kShortThreads, KIND == kPairWolf ? 7 : 8) k_sh
             int left = c4A - 1;
             for (int t0 = 0; t0 < T; t0 += 4) {
               const unsigned at = min(p + (jump & (unsigned)(left >> 31)), last);
-              short_pairs4<M, FORCES, POT, KIND>((const float4*)((const char*)&jbuf[0][0] + at), pi, a2b, K, ax, ay, az, ap);
+              short_pairs4<M, FORCES, POT, KIND>((const float4*)((const char*)jbuf + at), pi, a2b, K, ax, ay, az, ap);
               p += 4 * sizeof(float4);
               left -= 4;
             }
@@ -1565,13 +1584,13 @@ __global__ void __launch_bounds__(kShortThreads, KIND == kPairWolf ? 7 : 8) k_sh
           }
         }
         const int u0 = wave_min_s(lo), u1 = wave_max_s(hi);
-        for (int s0 = u0; s0 < u1; s0 += kShortSeg) {
+        for (int s0 = u0; s0 < u1; s0 += seg) {
           // stage the union of the windows, 256 atoms at a time
 #pragma unroll
           for (int v = 0; v < kShortSeg / kWave; ++v) {
             const int j = s0 + v * kWave + lane;
             float4 pj = make_float4(3e30f, 3e30f, 3e30f, 0.f);
-            if (j < u1) {
+            if (j < u1 && v * kWave < seg) {
               pj = sorted[j];
               if (PER) {
                 pj.x = shifted(pj.x, sx);
@@ -1579,11 +1598,11 @@ __global__ void __launch_bounds__(kShortThreads, KIND == kPairWolf ? 7 : 8) k_sh
                 pj.z = shifted(pj.z, sz);
               }
             }
-            jb[v * kWave + lane] = pj;
+            if (v * kWave < seg) jb[v * kWave + lane] = pj;
           }
-          if (lane < 4) jb[kShortSeg + lane] = make_float4(3e30f, 3e30f, 3e30f, 0.f);
+          if (lane < 4) jb[seg + lane] = make_float4(3e30f, 3e30f, 3e30f, 0.f);
           // this lane's part of the staged segment: [a0, a0 + n) (n = 0 keeps a0 = 0)
-          const int lo_s = max(lo, s0) - s0, hi_s = min(hi, s0 + kShortSeg) - s0;
+          const int lo_s = max(lo, s0) - s0, hi_s = min(hi, s0 + seg) - s0;
           const int n = (hi > lo && hi_s > lo_s) ? hi_s - lo_s : 0;
           const int a0 = n > 0 ? lo_s : 0;
           const int b0 = a0 + n;
@@ -1598,10 +1617,10 @@ __global__ void __launch_bounds__(kShortThreads, KIND == kPairWolf ? 7 : 8) k_sh
             }
             coincident |= zeros > ((i >= s0 + a0 && i < s0 + b0) ? 1 : 0);
           }
-          const unsigned last = base + kShortSeg * sizeof(float4);
+          const unsigned last = base + (unsigned)seg * sizeof(float4);
           unsigned p = base + (unsigned)a0 * sizeof(float4);
           for (int t0 = 0; t0 < nmax; t0 += 4) {
-            short_pairs4<M, FORCES, POT, KIND>((const float4*)((const char*)&jbuf[0][0] + min(p, last)), pi, a2b, K, ax, ay,
+            short_pairs4<M, FORCES, POT, KIND>((const float4*)((const char*)jbuf + min(p, last)), pi, a2b, K, ax, ay,
                                           az, ap);
             p += 4 * sizeof(float4);
           }
@@ -1609,21 +1628,43 @@ __global__ void __launch_bounds__(kShortThreads, KIND == kPairWolf ? 7 : 8) k_sh
         }
         }
       }
+      if (SPLIT && part_step < parts) {
+        float4* keep = jb + (kShortBuf - kWave) + lane;
+        if (part > part0) {
+          const float4 t = *keep;
+          ax = t.x + ax;
+          ay = t.y + ay;
+          az = t.z + az;
+          ap = t.w + ap;
+        }
+        if (part + part_step < parts) {
+          *keep = make_float4(ax, ay, az, ap);
+          ax = ay = az = ap = 0.f;
+        }
+      }
+      }
       if (coincident) atomicOr(S.d.status, kFlagCoincident);
-      // the waves' partial sums meet in the staging buffers (all waves are done with them)
-      float4* red = &jbuf[0][0];                       // kShortWaves x kWave entries
+      // the waves' partial sums meet in the staging buffers (all waves are done
+      // with them): the parts of each list of rows in order, then the lists
+      float4* red = jbuf;                              // waves x kWave entries
       __syncthreads();
-      red[wave * kWave + lane] = make_float4(ax, ay, az, ap);
+      red[slot * kWave + lane] = make_float4(ax, ay, az, ap);
       __syncthreads();
-      if (wave == 0 && live) {
-        float4 t = red[lane];
-#pragma unroll
-        for (int w = 1; w < kShortWaves; ++w) {
-          const float4 v = red[w * kWave + lane];
-          t.x += v.x;
-          t.y += v.y;
-          t.z += v.z;
-          t.w += v.w;
+      if (slot == 0 && live) {
+        float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int w = 0; w < kShortWaves; ++w) {
+          float4 l = red[w * kWave + lane];
+          for (int p = 1; p < part_step; ++p) {
+            const float4 v = red[(p * kShortWaves + w) * kWave + lane];
+            l.x += v.x;
+            l.y += v.y;
+            l.z += v.z;
+            l.w += v.w;
+          }
+          t.x += l.x;
+          t.y += l.y;
+          t.z += l.z;
+          t.w += l.w;
         }
         const float qi = pi.w;
         fshort[i] = make_float4(qi * t.x, qi * t.y, qi * t.z, t.w);
@@ -3456,18 +3497,29 @@ hipError_t launch_eval(int mode, const LaunchGeom& L, hipStream_t s, const Io& i
     const int slot = short_part++ == 0 ? kStageShort : kSlotShort2;
     beg(slot, ss);
     const KArgs A = args(L.shortr);
-    const int nb = L.shortr.blocks;
+    const int nb = L.shortr.blocks, nt = L.short_parts * kShortThreads;
+    const int lds = L.short_parts * kShortWaves * kShortBuf * (int)sizeof(float4);
     // Nobody reads the potential of an evaluation that returns neither
     // potentials nor an energy (the steps of a trajectory, an energy gradient
     // without dE/dq): those pairs sum forces alone (three velocity Verlet
     // steps of 50,000 atoms: 636 us; 664 with the potential).
     const bool pot = mode == kModeEnergy || io.phi != nullptr || io.energy != nullptr;
-#define MSM_SHORT_P(MM, FF, PP, KK)                                                     \
-  do {                                                                                  \
-    if (L.short_periodic)                                                               \
-      k_short<MM, FF, PP, KK, true><<<nb, kShortThreads, 0, ss>>>(A, lo_pm, hi_pm);      \
-    else                                                                                \
-      k_short<MM, FF, PP, KK, false><<<nb, kShortThreads, 0, ss>>>(A, lo_pm, hi_pm);     \
+#define MSM_SHORT_S(MM, FF, PP, KK, PE)                                                                      \
+  do {                                                                                                       \
+    if (L.short_split_rows) {                                                                                \
+      (void)hipFuncSetAttribute((const void*)k_short<MM, FF, PP, KK, PE, true>,                              \
+                                hipFuncAttributeMaxDynamicSharedMemorySize, lds);                            \
+      k_short<MM, FF, PP, KK, PE, true><<<nb, nt, lds, ss>>>(A, lo_pm, hi_pm);                               \
+    } else {                                                                                                 \
+      k_short<MM, FF, PP, KK, PE, false><<<nb, kShortThreads, 0, ss>>>(A, lo_pm, hi_pm);                     \
+    }                                                                                                        \
+  } while (0)
+#define MSM_SHORT_P(MM, FF, PP, KK)                                            \
+  do {                                                                         \
+    if (L.short_periodic)                                                      \
+      MSM_SHORT_S(MM, FF, PP, KK, true);                                       \
+    else                                                                       \
+      MSM_SHORT_S(MM, FF, PP, KK, false);                                      \
   } while (0)
 #define MSM_SHORT(MM)                                                          \
   do {                                                                         \
@@ -3496,6 +3548,7 @@ hipError_t launch_eval(int mode, const LaunchGeom& L, hipStream_t s, const Io& i
     }
 #undef MSM_SHORT
 #undef MSM_SHORT_P
+#undef MSM_SHORT_S
     end(slot, ss);
     if (short_side) (void)hipEventRecord(cc->shortr.join, ss);
   };

@@ -29,7 +29,8 @@ struct msm_plan {
   std::vector<double> top;                   // FP64 top-level kernel table
   int n_partials = 1;
   int bin2_blocks = 0;                       // blocks of the two-kernel binning where it is possible
-  bool prefer_bin2 = false;                  // two-kernel binning over one kernel where both work (batches)
+  bool in_batch = false;                     // one of several systems: two-kernel binning over one kernel where both
+                                             // work, and no spare short-range work items
   int max_cells = 0;                         // link cells of the finest cell reach (sizes the cell sections)
   long long max_bin_hist = 0;                // two-kernel histogram entries of any cell reach
   msm::LatLaunch lat;
