@@ -266,7 +266,10 @@ typedef struct msm_tuning {
                             (> 0), or -1 for one block per work item */
   int32_t streams;       /* 1: every stage in order on the caller's stream;
                             2: the short-range pass on a side stream;
-                            3: also the level-0 lattice cutoff on a side stream */
+                            3: also the level-0 lattice cutoff on a side stream.
+                            A plan or batch that was never given a value reports
+                            3 and leaves out the side streams that cost more
+                            host time than they hide at its size */
   int32_t short_after;   /* with a side stream, the short-range pass starts after
                             1: binning, 2: anterpolation, 3: the coarse lattice
                             cutoff (it then overlaps the prolongations) */

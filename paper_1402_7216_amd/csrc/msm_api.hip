@@ -432,7 +432,6 @@ void refresh_launch(msm_plan* P) {
   lg.lat_b = P->lat.b;
   lg.lat_lds = P->lat.lds_bytes;
   lg.max_levels = g.levels;
-  lg.streams = P->streams;
   lg.short_after = P->short_after;
   lg.short_split = P->short_split;
   lg.zero.blocks = sb.zero;
@@ -474,6 +473,8 @@ void refresh_launch(msm_plan* P) {
     lg.restrict_[k].blocks = sb.restrict_[k];
   }
   lg.prolong.blocks = sb.prolong;
+  lg.streams = lg.capture_streams = P->streams;
+  if (!P->streams_set) default_streams(lg, g.periodic != 0);
 }
 
 // Neighbour cell rows (offsets oy, oz in [-reach, reach], row index
@@ -619,6 +620,25 @@ void set_cell_geometry(msm_plan* P, int reach) {
 // tries the finer cells.
 int default_reach(int) { return 2; }
 
+// A side stream's fork and join take the host 20 to 35 us (each wait of a
+// stream for another's event 10 to 19, a launch 2.6), which is free only while
+// the device is busy with earlier work, or in a graph.
+//  - Systems whose rows are split finish the short range in 10 to 20 us: all on
+//    one stream (1,000 atoms: 71 us; 74 to 95 with one side stream, 92 to 119
+//    with two; 4,096 ions 75 us per step, 75 to 79, 99).  As a graph one side
+//    stream is right for them too (74 us against 77 and 84), and periodic ones
+//    take it always: their grid stages have twice the launches for the short
+//    range to hide behind (9,000 atoms: 139 us, 151 in order).
+//  - The level-0 lattice cutoff beside the coarse levels pays from about 1,000
+//    blocks (1,000,000 atoms, 1152 blocks: 1119 us, 1128 without; 100,000 atoms,
+//    864 blocks: 420 and 421; 50,000, 315 blocks: 622 and 616; 24,000, 324
+//    blocks: 112 and 106 as a graph).
+void default_streams(msm::LaunchGeom& L, bool periodic) {
+  L.streams = L.lattice0.blocks >= msm::kLattice0SideBlocks && !periodic ? 3 : 2;
+  L.capture_streams = L.streams;
+  if (L.short_parts > 1 && !periodic) L.streams = 1;
+}
+
 void retune(msm_plan* P, const msm_tuning& t) {
   if (t.cell_reach != 0 && t.cell_reach != P->g.reach) set_cell_geometry(P, t.cell_reach);
   if (t.lattice_b && P->lat.b && t.lattice_b != P->lat.b)
@@ -626,7 +646,10 @@ void retune(msm_plan* P, const msm_tuning& t) {
   Geom& g = P->g;
   if (t.item_chunks > 0) set_row_items(g, t.item_chunks, P->in_batch);
   if (t.short_blocks != 0) P->short_cap = t.short_blocks < 0 ? 0 : t.short_blocks;
-  if (t.streams != 0) P->streams = t.streams;
+  if (t.streams != 0) {
+    P->streams = t.streams;
+    P->streams_set = true;
+  }
   if (t.short_after != 0) P->short_after = t.short_after;
   if (t.short_split != 0) P->short_split = t.short_split;
   set_short_blocks(g, P->short_cap);
@@ -1138,7 +1161,8 @@ msm_status msm_plan_describe(const msm_plan* P, char* buf, size_t buf_bytes) {
        std::to_string(g.binr_blocks) +
        ", \"item_chunks\": " + std::to_string(g.item_chunks) + ", \"short_blocks\": " + std::to_string(g.short_blocks) +
        ", \"short_parts\": " + std::to_string(g.short_parts) +
-       ", \"streams\": " + std::to_string(P->streams) + ", \"short_after\": " + std::to_string(P->short_after) +
+       ", \"streams\": " + std::to_string(P->streams) + ", \"layout\": " + std::to_string(P->lg.streams) +
+       ", \"graph_layout\": " + std::to_string(P->lg.capture_streams) + ", \"short_after\": " + std::to_string(P->short_after) +
        ", \"short_split\": " + std::to_string(P->short_split);
   o += ", \"taps\": " + std::to_string(P->weights.size()) + ", \"halo\": " + std::to_string(P->lat.H);
   o += ", \"lattice_b\": " + std::to_string(P->lat.b) + ", \"lattice_waves\": " + std::to_string(P->lat.b > 0 ? msm::lat_waves(P->lat.b) : 0) +
@@ -1314,7 +1338,8 @@ msm_status msm_graph_capture(const msm_plan* P, void* ws, size_t ws_bytes, const
   hipError_t e = ensure_aux(M->aux);
   if (e != hipSuccess) return hip_fail(e, "create auxiliary stream");
   const msm::Io io{x, y, z, q, fx, fy, fz, phi, energy, virial, nullptr};
-  const msm::LaunchGeom L = launch_geom(P, ws);
+  msm::LaunchGeom L = launch_geom(P, ws);
+  L.streams = L.capture_streams;
   return capture_graph(
       [&](hipStream_t cs) {
         return msm::launch_eval(msm::kModeForces, L, cs, io, nullptr, &M->aux.cc);

@@ -113,7 +113,6 @@ void rebuild_maps(msm_batch* Bt) {
   L.n_sys = Bt->n_sys;
   L.order = Bt->plans[0]->g.order;
   L.m = Bt->plans[0]->g.m;
-  L.streams = Bt->plans[0]->streams;
   L.short_after = Bt->plans[0]->short_after;
   L.short_split = Bt->plans[0]->short_split;
   L.lat_b = 0;
@@ -138,10 +137,12 @@ void rebuild_maps(msm_batch* Bt) {
   // blocks of more waves where the whole batch still is a small launch of
   // systems that split their rows; else a wave takes all parts of its rows
   L.short_parts = L.shortr.blocks <= 2 * msm::kShortSmallItems ? msm::kShortParts : 1;
+  L.streams = L.capture_streams = Bt->plans[0]->streams;
   for (const msm_plan* P : Bt->plans) {
     L.short_parts = std::min(L.short_parts, P->g.short_parts);
     L.short_split_rows |= P->g.short_parts > 1;
   }
+  if (!Bt->plans[0]->streams_set) default_streams(L, false);
 }
 
 void point_into(msm_batch* Bt, void* ws, msm::LaunchGeom& L) {
@@ -357,12 +358,14 @@ static msm_status batch_eval(int mode, const msm_batch* Bt, void* ws, size_t ws_
   if (e != hipSuccess) return hip_fail(e, "create auxiliary stream");
   msm::LaunchGeom L = Bt->lg;
   point_into(M, ws, L);
-  if (graph)
+  if (graph) {
+    L.streams = L.capture_streams;
     return capture_graph(
         [&](hipStream_t cs) {
           return msm::launch_eval(mode, L, cs, io, nullptr, &M->aux.cc);
         },
         &M->tune_gen, graph);
+  }
   e = msm::launch_eval(mode, L, reinterpret_cast<hipStream_t>(stream), io, nullptr, &M->aux.cc);
   if (e != hipSuccess) return hip_fail(e, "kernel launch");
   return MSM_OK;

@@ -15,6 +15,7 @@ constexpr int kMaxLevels = 12;
 constexpr int kShortWaves = 4;           // waves of a short-range block (they split the neighbour rows)
 constexpr int kShortParts = 4;           // parts a small system sums a wave's rows in, side by side in blocks of 16 waves
 constexpr int kShortSmallItems = 256;    // short-range work items up to which a system is small (one block per CU)
+constexpr int kLattice0SideBlocks = 1024; // level-0 lattice blocks from which that launch gets a stream of its own
 constexpr int kShortRowsPerWave = 24;    // neighbour rows one wave can take
 constexpr int kMaxOrder = 6;
 constexpr int kMaxTopNodes = 1 << 17;     // all-pairs FP64 top level stays below ~1e10 pair terms
@@ -325,6 +326,7 @@ struct LaunchGeom {
   int lat_lds = 0;                   // dynamic LDS of the tiled kernel
   int max_levels = 1;
   int streams = 3;                   // 1: in order; 2: short range on a side stream; 3: also level-0 lattice
+  int capture_streams = 3;           // the same in a captured graph
   int short_after = 1;               // side-stream short range starts after 1: binning, 2: anterpolation,
                                      // 3: the coarse lattice cutoff
   int short_split = 1000;            // per mille of its work items started there (the rest after the

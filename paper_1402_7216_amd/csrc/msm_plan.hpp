@@ -37,6 +37,7 @@ struct msm_plan {
   int lat_part_max = 0;                      // lattice phase-group partials of the largest tuning
   int short_cap = 0;                         // short-range blocks (0: one per work item)
   int streams = 3;                           // stream layout of an evaluation (msm_tuning.streams)
+  bool streams_set = false;                  // chosen by the caller, the autotuner or a cache (else by size)
   int short_after = 1;                       // start of the side-stream short range (msm_tuning.short_after)
   int short_split = 1000;                    // per mille of it started there (msm_tuning.short_split)
   uint64_t tune_gen = 0;                     // bumped by every tuning change (graphs record it)
@@ -85,6 +86,9 @@ void refresh_launch(msm_plan* P);
 // short-range rows, work items and binning path they imply.
 void set_cell_geometry(msm_plan* P, int reach);
 int default_reach(int n_atoms);
+// Stream layouts of plans and batches nobody chose one for, for calls and for
+// captured graphs (short_parts and blocks are those of the whole launch).
+void default_streams(msm::LaunchGeom& L, bool periodic);
 
 // Number of systems and total atom count of a batch (the concatenated arrays'
 // length).
