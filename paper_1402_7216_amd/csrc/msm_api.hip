@@ -296,8 +296,6 @@ void choose_lattice_tiles(const Geom& g, int H_, msm::LatLaunch& lat, int force_
   lat.lds_bytes = msm::lat_lds(H_, B);
   std::vector<double> mat(phases);                         // fragment pairs of each phase's slowest wave
   for (int ph = 0; ph < phases; ++ph) mat[ph] = cut_rows(lat, ph);
-  // the partials live where the anterpolation's did, or in 8 MiB
-  const double part_cap = std::max((double)g.atn[0] * g.atn[1] * g.atn[2] * g.at_ext, 1048576.0);
   // blocks on the chip at a time (two on a CU share its matrix pipes)
   const int slots = 256 * (B < 8 && 2 * (lat.lds_bytes + 4096) <= 160 * 1024 ? 2 : 1);
   int blocks = 0;
@@ -308,7 +306,7 @@ void choose_lattice_tiles(const Geom& g, int H_, msm::LatLaunch& lat, int force_
     const double tiles = tiles_of(k, B, t);
     double best = 1e300;
     for (int G = 1; G <= std::min(msm::kLatMaxGroups, phases); ++G) {
-      if (G > 1 && lat.n_part + (double)G * L.count > part_cap) break;
+      if (G > 1 && lat.n_part + (double)G * L.count > (double)g.part_cap) break;
       double sum = 0.0, longest = 0.0;
       for (int q = 0; q < G; ++q) {
         double blk = 9000.0;
@@ -620,6 +618,36 @@ void set_cell_geometry(msm_plan* P, int reach) {
 // tries the finer cells.
 int default_reach(int) { return 2; }
 
+// Anterpolation tiles: start from 16 x 16 x 8 level-0 nodes and halve the
+// largest side until there are at least `target` tiles (a launch then covers
+// the 256 compute units twice).  Sides below 4 only while a tile has 128 atoms
+// or more (a coarse grid, e.g. h = 10 A, has few nodes but as many atoms): the
+// regions of smaller tiles are mostly overlap, which the gather adds up again
+// (1,000 atoms on 12 nodes a side, tiles of 1 and of 4: anterpolation 6.6 and
+// 6.8 us, gather 13.4 and 4.6; 9,000 atoms, order 6, tiles of 2 and 4: 17.0 and
+// 10.5, 11.5 and 9.2).
+void set_anterp_tiles(Geom& g, int target) {
+  int t[3] = {16, 16, 8};
+  auto tiles = [&]() {
+    long long n = 1;
+    for (int d = 0; d < 3; ++d) n *= (g.fmax[d] + t[d]) / t[d];
+    return n;
+  };
+  while (tiles() < target) {
+    int d = 0;
+    for (int e = 1; e < 3; ++e)
+      if (t[e] > t[d]) d = e;
+    if (t[d] <= 1 || (t[d] <= 4 && g.n_atoms < 128 * tiles())) break;
+    t[d] /= 2;
+  }
+  g.at_ext = 1;
+  for (int d = 0; d < 3; ++d) {
+    g.at[d] = t[d];
+    g.atn[d] = (g.fmax[d] + t[d]) / t[d];              // tiles covering floor indices 0 .. fmax
+    g.at_ext *= t[d] + g.order - 1;
+  }
+}
+
 // A side stream's fork and join take the host 20 to 35 us (each wait of a
 // stream for another's event 10 to 19, a launch 2.6), which is free only while
 // the device is busy with earlier work, or in a graph.
@@ -869,31 +897,9 @@ msm_status msm_plan_create(const msm_params* prm, int32_t n_atoms, msm_plan** ou
     return fail(MSM_ERR_UNSUPPORTED, "top level too large for the all-pairs sum; use more levels");
   }
 
-  // anterpolation tiles: start from 16 x 16 x 8 level-0 nodes and halve the
-  // largest side (down to 1) until there are at least 512 tiles, so a launch
-  // covers the 256 compute units twice (a coarse grid, e.g. h = 10 A, has few
-  // nodes but as many atoms: its tiles shrink to a few nodes each)
-  {
-    int t[3] = {16, 16, 8};
-    auto tiles = [&]() {
-      long long n = 1;
-      for (int d = 0; d < 3; ++d) n *= (g.fmax[d] + t[d]) / t[d];
-      return n;
-    };
-    while (tiles() < 512) {
-      int d = 0;
-      for (int e = 1; e < 3; ++e)
-        if (t[e] > t[d]) d = e;
-      if (t[d] <= 1) break;
-      t[d] /= 2;
-    }
-    g.at_ext = 1;
-    for (int d = 0; d < 3; ++d) {
-      g.at[d] = t[d];
-      g.atn[d] = (g.fmax[d] + t[d]) / t[d];          // tiles covering floor indices 0 .. fmax
-      g.at_ext *= t[d] + p.order - 1;
-    }
-  }
+  set_anterp_tiles(g, msm::kAntTiles);
+  // the lattice cutoff's partials live where the anterpolation's did, or in 8 MiB
+  g.part_cap = std::max((long long)g.atn[0] * g.atn[1] * g.atn[2] * g.at_ext, 1048576LL);
 
   // smoothing constants
   double c[9];

@@ -15,6 +15,8 @@ constexpr int kMaxLevels = 12;
 constexpr int kShortWaves = 4;           // waves of a short-range block (they split the neighbour rows)
 constexpr int kShortParts = 4;           // parts a small system sums a wave's rows in, side by side in blocks of 16 waves
 constexpr int kShortSmallItems = 256;    // short-range work items up to which a system is small (one block per CU)
+constexpr int kAntTiles = 512;           // anterpolation tiles of a system, at least (where the grid has the nodes)
+constexpr int kAntBatchTiles = 1024;     // tiles of a batch, shared by its systems
 constexpr int kLattice0SideBlocks = 1024; // level-0 lattice blocks from which that launch gets a stream of its own
 constexpr int kShortRowsPerWave = 24;    // neighbour rows one wave can take
 constexpr int kMaxOrder = 6;
@@ -97,6 +99,7 @@ struct Geom {
   float dr[8];                     // 2 k c_k / a^(2k+1)   (gamma'(r/a)/(a^2 r) = sum_{k>=1} dr[k] r^2(k-1))
   int at[3];                       // anterpolation node tile (level-0 nodes per dimension)
   int atn[3];                      // anterpolation tiles per dimension (they own floor indices 0..fmax)
+  long long part_cap;              // float32 partials the lattice cutoff's phase groups may use
   int at_ext;                      // nodes of a tile's private region (at[d] + order - 1 per dimension)
   int pair;                        // 0: MSM; else the cheap pair method evaluated alone (kPair*)
   float pk[4];                     // constants of the pair method (see k_short)

@@ -86,6 +86,7 @@ void refresh_launch(msm_plan* P);
 // short-range rows, work items and binning path they imply.
 void set_cell_geometry(msm_plan* P, int reach);
 int default_reach(int n_atoms);
+void set_anterp_tiles(Geom& g, int target);
 // Stream layouts of plans and batches nobody chose one for, for calls and for
 // captured graphs (short_parts and blocks are those of the whole launch).
 void default_streams(msm::LaunchGeom& L, bool periodic);
