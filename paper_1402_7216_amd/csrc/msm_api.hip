@@ -451,8 +451,8 @@ void refresh_launch(msm_plan* P) {
   // rebuild boxes of up to (2R + 3)^3 nodes on every coarser level)
   int tiles0 = 0;
   for (int k = 0; k + 1 < g.levels; ++k) {
-    lg.prolong_level[k] = msm::prolong_level_blocks(g, k);
-    if (k == 0) tiles0 = lg.prolong_level[k];
+    lg.prolong_level[k].blocks = sb.prolong_level[k];
+    if (k == 0) tiles0 = sb.prolong_level[k];
   }
   lg.prolong_split = g.levels > 1 && (tiles0 >= msm::kProlongSplitTiles || g.periodic);
   lg.periodic = g.periodic && !g.pair;

@@ -37,7 +37,9 @@ constexpr int kStatusUnranked = 1;        // status word: some cell kept its sca
                                           // coincident atoms by binning)
 constexpr int kScanTile = 4096;           // cells per block of the four-kernel binning's scan
 constexpr int kXcds = 8;                  // accelerator dies of the chip, each with its own L2
-constexpr int kProlongSplitTiles = 1000;  // level-0 prolongation tiles from which each level gets its own launch
+constexpr int kProlongSplitTiles = 300;  // level-0 prolongation tiles from which each level gets its own launch (16 small
+                                         // systems, 500 tiles: 416 us, 425 with one launch; 24,000 atoms, 125 tiles: 110
+                                         // and 106 as a graph, so no less)
 
 enum DeviceFlag : int { kFlagOutOfBox = 1, kFlagNonFinite = 2, kFlagCoincident = 4, kFlagBadExclusion = 8 };
 
@@ -340,8 +342,8 @@ struct LaunchGeom {
   StageGrid scan;                    // tiles of the four-kernel binning's cell-count scan
   StageGrid agather;                 // level-0 nodes (gather of the anterpolation partials)
   int anterp_lds = 0;                // dynamic LDS of the anterpolation (largest system)
-  bool prolong_split = false;        // one prolongation launch per level (one large system)
-  int prolong_level[kMaxLevels] = {};   // prolongation tiles of each level below the top
+  bool prolong_split = false;        // one prolongation launch per level (large grids)
+  StageGrid prolong_level[kMaxLevels];  // prolongation tiles of each level below the top
   StageGrid bin;                     // two-kernel binning (systems with bin_blocks > 0)
   StageGrid binrow;                  // one-kernel binning (systems with bin_row_blocks > 0)
   StageGrid rchunk;                  // row binning: count and scatter (systems with binr_blocks > 0)
@@ -367,9 +369,9 @@ struct SysBlocks {
   int rchunk, rscan, rsort;          // row binning
   int restrict_[kMaxLevels];
   int prolong;                       // tiles of every level below the top
+  int prolong_level[kMaxLevels];     // the same, of each level
 };
 SysBlocks system_blocks(const Geom& g, const LatLaunch& lat, int n_partials);
-int prolong_level_blocks(const Geom& g, int k);   // prolongation tiles of level k
 
 // Dynamic LDS of the one-kernel binning for one system: per-wave counts of the
 // cells a block owns, scan scratch, and a 16-bit list entry per atom.

@@ -3374,7 +3374,8 @@ SysBlocks system_blocks(const Geom& g, const LatLaunch& lat, int n_partials) {
   for (int k = 0; k + 1 < g.levels; ++k) {
     const Level& C = g.lv[k + 1];
     b.restrict_[k] = ((C.n[0] + kRX - 1) / kRX) * ((C.n[1] + kRY - 1) / kRY) * ((C.n[2] + kRZ - 1) / kRZ);
-    b.prolong += prolong_tiles(g.lv[k]);
+    b.prolong_level[k] = prolong_tiles(g.lv[k]);
+    b.prolong += b.prolong_level[k];
   }
   // lattice cutoff in two launches: level 0, and levels 1 .. l-2
   if (g.levels > 1) {
@@ -3401,8 +3402,6 @@ SysBlocks system_blocks(const Geom& g, const LatLaunch& lat, int n_partials) {
   b.energy = n_partials;
   return b;
 }
-
-int prolong_level_blocks(const Geom& g, int k) { return prolong_tiles(g.lv[k]); }
 
 hipError_t launch_init(const LaunchGeom& L, hipStream_t s) {
   if (L.zero.blocks > 0) k_zero_counts<<<L.zero.blocks, kBlock, 0, s>>>(KArgs{L.sys, L.zero.map, Io{}});
@@ -3666,14 +3665,14 @@ hipError_t launch_eval(int mode, const LaunchGeom& L, hipStream_t s, const Io& i
   mark(kStageProlong);
   if (lat0_side) join(cc->lattice0);                 // u^0 adds the level-0 cutoff potential
   beg(kStageProlong, s);
-  if (L.prolong.blocks > 0 && L.prolong_split) {
-    // one launch per level, coarse to fine (a single system: no block tables)
+  if (L.prolong_split) {
+    // one launch per level, coarse to fine
     const int lds = 2 * prolong_box(L.order) * (int)sizeof(float);             // one box + x-pass sums
     for (int k = L.max_levels - 2; k >= 0; --k) {
-      const int nb = L.prolong_level[k];
+      const int nb = L.prolong_level[k].blocks;
       if (nb == 0) continue;
       ghosts(k + 1, kGhostU, 0);
-      const KArgs A{L.sys, nullptr, io};
+      const KArgs A = args(L.prolong_level[k]);
       if (L.order == 4)
         k_prolong<4, true><<<nb, kPThreads, lds, s>>>(A, k);
       else
