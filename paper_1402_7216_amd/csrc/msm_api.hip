@@ -457,7 +457,6 @@ void refresh_launch(msm_plan* P) {
   lg.prolong_split = g.levels > 1 && (tiles0 >= msm::kProlongSplitTiles || g.periodic);
   lg.periodic = g.periodic && !g.pair;
   lg.short_periodic = g.periodic != 0;
-  for (int k = 0; k < g.levels; ++k) lg.ghost_blocks[k] = lg.periodic ? (g.lv[k].count + 255) / 256 : 0;
   lg.shortr.blocks = sb.shortr;
   lg.short_parts = g.short_parts;
   lg.short_split_rows = g.short_parts > 1;

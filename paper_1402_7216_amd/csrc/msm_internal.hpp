@@ -350,9 +350,8 @@ struct LaunchGeom {
   StageGrid rscan;                   // row binning: one block per system
   StageGrid rsort;                   // row binning: one block per cell row
   int rsort_lds = 0;                 // dynamic LDS of the row binning's sort (largest system)
-  bool periodic = false;             // periodic grids: ghost folds and fills between the stages
+  bool periodic = false;             // periodic grids: the level-0 charges of the images are folded in
   bool short_periodic = false;       // periodic short range (MSM or pair plans)
-  int ghost_blocks[kMaxLevels] = {}; // blocks of a ghost fill of each level (one system)
   int binrow_lds = 0;                // dynamic LDS of the one-kernel binning (largest system)
   bool bin4 = true;                  // some system uses the four-kernel binning
   StageGrid lattice0;                // lattice cutoff of level 0

@@ -1960,8 +1960,10 @@ __global__ void __launch_bounds__(kBlock) k_anterp_gather(KArgs A) {
     t0[d] = max(0, (m[d] - (ORDER - 1)) / g.at[d]);
     if (m[d] < ORDER - 1) t0[d] = 0;
   }
+  // a periodic level's sums wait in u^0 for k_fold
+  float* __restrict__ out = (g.periodic ? S.d.u : S.d.qgrid) + L.off;
   if (!any) {
-    S.d.qgrid[L.off + node] = 0.f;
+    out[node] = 0.f;
     return;
   }
   const int ex = g.at[0] + ORDER - 1, ey = g.at[1] + ORDER - 1;
@@ -1974,7 +1976,54 @@ __global__ void __launch_bounds__(kBlock) k_anterp_gather(KArgs A) {
         const int lx = m[0] - tx * g.at[0], ly = m[1] - ty * g.at[1], lz = m[2] - tz * g.at[2];
         sum += part[(size_t)tile * g.at_ext + (lz * ey + ly) * ex + lx];
       }
-  S.d.qgrid[L.off + node] = (float)((double)sum * kInvFix);
+  out[node] = (float)((double)sum * kInvFix);
+}
+
+// --------------------------------------------------------------------------
+// Ghost nodes of a periodic level: the nodes outside one period (indices from
+// -ghost up) stand for nodes of the period.  The kernel that computes a node
+// of the period also writes its images: a launch that only copied them took
+// about 4 us, and an evaluation had one after every stage (9,000 atoms: seven,
+// 27 of 163 us of kernels and as many gaps; 127 us an evaluation, 122 without).
+// --------------------------------------------------------------------------
+// The images of a node i of the period [0, p) along one dimension, itself
+// included: i + j p for j = first .. first + count - 1, those in [-G, p + G).
+struct ImageRange {
+  int first, count;
+};
+__device__ __forceinline__ ImageRange image_range(int i, int p, int G) {
+  const float inv_p = 1.f / (float)p;
+  int rem;
+  const int below = fdiv(i + G, p, inv_p, rem), above = fdiv(p + G - 1 - i, p, inv_p, rem);
+  return {-below, below + above + 1};
+}
+
+// f(offset) for the node (ix, iy, iz) of the period, then for every image of
+// it among the level's nodes [-G, period + G).  Several threads may share the
+// images of a node: this one takes image `sub` and every `step`-th after it
+// (and the node itself if sub is 0).
+template <class F>
+__device__ __forceinline__ void each_image(const Level& L, int G, int ix, int iy, int iz, F f, int sub = 0,
+                                           int step = 1) {
+  const ImageRange x = image_range(ix, L.per[0], G), y = image_range(iy, L.per[1], G), z = image_range(iz, L.per[2], G);
+  const float inv_x = 1.f / (float)x.count, inv_y = 1.f / (float)y.count;
+  auto at = [&](int jx, int jy, int jz) {
+    return ((iz + G + jz * L.per[2]) * L.n[1] + (iy + G + jy * L.per[1])) * L.n[0] + (ix + G + jx * L.per[0]);
+  };
+  if (sub == 0) f(at(0, 0, 0));
+  for (int i = sub; i < x.count * y.count * z.count; i += step) {
+    int jx, jy;
+    int jz = fdiv(fdiv(i, x.count, inv_x, jx), y.count, inv_y, jy);
+    jx += x.first;
+    jy += y.first;
+    jz += z.first;
+    if (jx || jy || jz) f(at(jx, jy, jz));
+  }
+}
+
+// Whether a tile of level-local nodes [lo, lo + ext) holds a node of the period.
+__device__ __forceinline__ bool in_period(const Level& L, int G, int bx, int ex, int by, int ey, int bz, int ez) {
+  return bx + ex > G && bx < G + L.per[0] && by + ey > G && by < G + L.per[1] && bz + ez > G && bz < G + L.per[2];
 }
 
 // --------------------------------------------------------------------------
@@ -2032,6 +2081,8 @@ __global__ void __launch_bounds__(kRThreads) k_restrict(KArgs A, int k) {
   const int ntx = (C.n[0] + kRX - 1) / kRX, nty = (C.n[1] + kRY - 1) / kRY;
   const int bx = blk % ntx, by = (blk / ntx) % nty, bz = blk / (ntx * nty);
   const int c0x = bx * kRX, c0y = by * kRY, c0z = bz * kRZ;          // level-local coarse origin
+  const int G = g.ghost;
+  if (g.periodic && !in_period(C, G, c0x, kRX, c0y, kRY, c0z, kRZ)) return;   // images only
   // absolute fine index of local fine (0,0,0): 2 (C.lo + c0) - R
   const int f0x = 2 * (C.lo[0] + c0x) - R, f0y = 2 * (C.lo[1] + c0y) - R, f0z = 2 * (C.lo[2] + c0z) - R;
   const float* fin = grid + F.off;
@@ -2071,10 +2122,11 @@ __global__ void __launch_bounds__(kRThreads) k_restrict(KArgs A, int k) {
     xs[i] = racc;
   }
   __syncthreads();
-  if (threadIdx.x >= kRX * kRY * kRZ) return;
-  const int tx = threadIdx.x % kRX, ty = (threadIdx.x / kRX) % kRY, tz = threadIdx.x / (kRX * kRY);
+  constexpr int kNodes = kRX * kRY * kRZ;
+  if (!g.periodic && threadIdx.x >= kNodes) return;
+  const int tx = threadIdx.x % kRX, ty = (threadIdx.x / kRX) % kRY, tz = threadIdx.x / (kRX * kRY) % kRZ;
   const int mx = c0x + tx, my = c0y + ty, mz = c0z + tz;
-  if (tz >= kRZ || mx >= C.n[0] || my >= C.n[1] || mz >= C.n[2]) return;
+  if (mx >= C.n[0] || my >= C.n[1] || mz >= C.n[2]) return;
   // then sum_{a, b} (w_b w_a) xs[2 tz + R + j_a][2 ty + R + j_b][tx] (a, then b
   // ascending): the operations of the direct triple sum, in its order
   float r[D::NT][D::NT];
@@ -2088,7 +2140,12 @@ __global__ void __launch_bounds__(kRThreads) k_restrict(KArgs A, int k) {
   for (int a = 0; a < D::NT; ++a)
 #pragma unroll
     for (int b = 0; b < D::NT; ++b) acc = fmaf(D::w(b) * D::w(a), r[a][b], acc);
-  grid[C.off + ((size_t)mz * C.n[1] + my) * C.n[0] + mx] = acc;
+  if (!g.periodic)
+    grid[C.off + ((size_t)mz * C.n[1] + my) * C.n[0] + mx] = acc;
+  else if (in_period(C, G, mx, 1, my, 1, mz, 1))
+    // (the sixteen threads that computed this node share its images)
+    each_image(C, G, mx - G, my - G, mz - G, [&](int at) { grid[C.off + at] = acc; }, threadIdx.x / kNodes,
+               kRThreads / kNodes);
 }
 
 // --------------------------------------------------------------------------
@@ -2100,7 +2157,7 @@ __global__ void __launch_bounds__(kRThreads) k_restrict(KArgs A, int k) {
 // kernel, as its own launch.
 // --------------------------------------------------------------------------
 // Periodic plans: the outputs and inputs are the nodes of one period (the
-// ghost copies are filled afterwards) and T holds the image sum K at the node
+// images of an output are written with it) and T holds the image sum K at the node
 // offsets (mu - nu) modulo the period.
 __device__ __forceinline__ void top_node_periodic(const SysDesc& S, const Level& L, int mx, int my, int mz,
                                                   int lane) {
@@ -2137,11 +2194,10 @@ __device__ __forceinline__ void top_node_periodic(const SysDesc& S, const Level&
   }
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off);
-  if (lane == 0) {
-    const size_t node = ((size_t)(mz + G) * L.n[1] + (my + G)) * L.n[0] + (mx + G);
-    S.d.ucut[L.off + node] = (float)acc;
-    S.d.u[L.off + node] = (float)acc;
-  }
+  each_image(L, G, mx, my, mz, [&](int at) {
+    S.d.ucut[L.off + at] = (float)acc;
+    S.d.u[L.off + at] = (float)acc;
+  }, lane, kWave);
 }
 
 __device__ __forceinline__ void top_node(const SysDesc& S, int node, int lane) {
@@ -2184,44 +2240,26 @@ __device__ __forceinline__ void top_node(const SysDesc& S, int node, int lane) {
   }
 }
 
-// --------------------------------------------------------------------------
-// Ghost nodes of a periodic level: the nodes outside one period (indices from
-// -ghost up) stand for nodes of the period.  fold: every node of the period
-// adds what its ghost images received (anterpolation spreads the atoms near a
-// face onto them), images in a fixed order; fill: every ghost node takes the
-// value of its node in the period.  One thread per node of the level (one
+// Level-0 charges of a periodic plan: every node of the period adds what its
+// images received (anterpolation spreads the atoms near a face onto them),
+// images in a fixed order, and the images take the sum.  The gather left the
+// level's own sums in u^0; one thread per node of the level, images too (one
 // system: periodic plans are not batched).
-// --------------------------------------------------------------------------
-enum GhostGrid : int { kGhostQ = 0, kGhostU = 1 };
-
-__global__ void __launch_bounds__(kBlock) k_ghost(KArgs A, int level, int which, int fold) {
+__global__ void __launch_bounds__(kBlock) k_fold(KArgs A) {
   const SysDesc& S = A.sys[0];
   const Geom& g = S.g;
-  const Level L = g.lv[level];
+  const Level L = g.lv[0];
   const int node = (int)blockIdx.x * kBlock + (int)threadIdx.x;
   if (node >= L.count) return;
-  float* grid = (which == kGhostQ ? S.d.qgrid : S.d.u) + L.off;
   const int G = g.ghost;
-  const int mx = node % L.n[0], my = (node / L.n[0]) % L.n[1], mz = node / (L.n[0] * L.n[1]);
-  const int ix = mx - G, iy = my - G, iz = mz - G;
-  const int p0 = L.per[0], p1 = L.per[1], p2 = L.per[2];
-  const bool inside = ix >= 0 && iy >= 0 && iz >= 0 && ix < p0 && iy < p1 && iz < p2;
-  auto at = [&](int x, int y, int z) { return ((size_t)(z + G) * L.n[1] + (y + G)) * L.n[0] + (x + G); };
-  if (fold) {
-    if (!inside) return;
-    // images x + j p of this node inside the level's nodes [-G, p + G)
-    auto jlo = [G](int x, int p) { return -((x + G) / p); };
-    auto jhi = [G](int x, int p) { return (p + G - 1 - x) / p; };
-    float v = grid[node];
-    for (int jz = jlo(iz, p2); jz <= jhi(iz, p2); ++jz)
-      for (int jy = jlo(iy, p1); jy <= jhi(iy, p1); ++jy)
-        for (int jx = jlo(ix, p0); jx <= jhi(ix, p0); ++jx)
-          if (jx || jy || jz) v += grid[at(ix + jx * p0, iy + jy * p1, iz + jz * p2)];
-    grid[node] = v;
-  } else if (!inside) {
-    const int wx = ((ix % p0) + p0) % p0, wy = ((iy % p1) + p1) % p1, wz = ((iz % p2) + p2) % p2;
-    grid[node] = grid[at(wx, wy, wz)];
-  }
+  const float inv_n0 = 1.f / (float)L.n[0], inv_n1 = 1.f / (float)L.n[1];
+  int mx, my;
+  const int mz = fdiv(fdiv(node, L.n[0], inv_n0, mx), L.n[1], inv_n1, my);
+  auto wrap = [G](int m, int p) { const int i = (m - G) % p; return i < 0 ? i + p : i; };
+  const float* __restrict__ raw = S.d.u + L.off;
+  float v = 0.f;
+  each_image(L, G, wrap(mx, L.per[0]), wrap(my, L.per[1]), wrap(mz, L.per[2]), [&](int at) { v += raw[at]; });
+  S.d.qgrid[L.off + node] = v;
 }
 
 __global__ void __launch_bounds__(kBlock) k_top(KArgs A) {
@@ -2405,8 +2443,8 @@ __global__ void __launch_bounds__(ZS * 4 * kWave, 2) k_lattice_mfma(KArgs A, int
   const int lv_off = uniform(g.lv[level].off);
   const int tile = bid / G, grp = bid - tile * G;
   const int bz = tile / (ntx * nty), by = (tile - bz * ntx * nty) / ntx, bx = tile - (bz * nty + by) * ntx;
-  // a periodic level's outputs are the nodes of one period (the ghost copies
-  // of u^k are filled afterwards), from the multiple of 8 below it along x, so
+  // a periodic level's outputs are the nodes of one period (the prolongation
+  // writes the images of u^k), from the multiple of 8 below it along x, so
   // that octets do not straddle the level's first node
   const int ghost = uniform(g.periodic) ? uniform(g.ghost) : 0;
   const int x0 = (ghost & ~7) + 16 * bx, y0 = ghost + 16 * by, z0 = ghost + ZB * ZS * bz;
@@ -2770,7 +2808,11 @@ k_prolong(KArgs A, int level) {
   const int to[3] = {F.lo[0] + bx * kPX, F.lo[1] + by * kPY, F.lo[2] + bz * kPZ};   // absolute
   const int tx = threadIdx.x % kPX, ty = (threadIdx.x / kPX) % kPY, tz = threadIdx.x / (kPX * kPY);
   const int fx = bx * kPX + tx, fy = by * kPY + ty, fz = bz * kPZ + tz;          // level-local
-  const bool inside = fx < F.n[0] && fy < F.n[1] && fz < F.n[2];
+  // periodic: the nodes of the period, whose images they write too
+  const int G = g.ghost;
+  if (g.periodic && !in_period(F, G, bx * kPX, kPX, by * kPY, kPY, bz * kPZ, kPZ)) return;
+  const bool inside = fx < F.n[0] && fy < F.n[1] && fz < F.n[2] &&
+                      (!g.periodic || in_period(F, G, fx, 1, fy, 1, fz, 1));
   const int node = (fz * F.n[1] + fy) * F.n[0] + fx;
   const float own = inside ? ucut_value(S, k, node, false) : 0.f;   // stored with u^k at the end
   // Fill the boxes, LV of them per round of loads: u^{l-1} for the top box,
@@ -2870,7 +2912,11 @@ k_prolong(KArgs A, int level) {
     __syncthreads();
     if (!inside) return;
     const int m[3] = {to[0] + tx, to[1] + ty, to[2] + tz};
-    u[F.off + (size_t)node] = own + prolong_yz<ORDER>(xs, co, ce, te, m, tx);
+    const float v = own + prolong_yz<ORDER>(xs, co, ce, te, m, tx);
+    if (!g.periodic)
+      u[F.off + (size_t)node] = v;
+    else
+      each_image(F, G, fx - G, fy - G, fz - G, [&](int at) { u[F.off + at] = v; });
   }
   if (!(S.lat.b == 0 || k >= S.lat.n) && S.lat.t[k].groups > 1) S.d.ucut[F.off + (size_t)node] = own;
 }
@@ -3579,13 +3625,7 @@ hipError_t launch_eval(int mode, const LaunchGeom& L, hipStream_t s, const Io& i
     k_anterp<6><<<L.anterp.blocks, kAThreads, L.anterp_lds, s>>>(args(L.anterp));
     k_anterp_gather<6><<<L.agather.blocks, kBlock, 0, s>>>(args(L.agather));
   }
-  // periodic: ghost copies of level k's grid of `which` (fold: gather them first)
-  const KArgs one_sys{L.sys, nullptr, io};
-  auto ghosts = [&](int k, int which, int fold) {
-    if (L.periodic && L.ghost_blocks[k] > 0) k_ghost<<<L.ghost_blocks[k], kBlock, 0, s>>>(one_sys, k, which, fold);
-  };
-  ghosts(0, kGhostQ, 1);
-  ghosts(0, kGhostQ, 0);
+  if (L.periodic) k_fold<<<L.agather.blocks, kBlock, 0, s>>>(args(L.agather));
   end(kStageAnterp, s);
   if (short_at == 2) launch_short(0, split);
 
@@ -3631,7 +3671,6 @@ hipError_t launch_eval(int mode, const LaunchGeom& L, hipStream_t s, const Io& i
       k_restrict<4><<<sg.blocks, kRThreads, 0, s>>>(args(sg), k);
     else
       k_restrict<6><<<sg.blocks, kRThreads, 0, s>>>(args(sg), k);
-    ghosts(k + 1, kGhostQ, 0);
   }
   end(kStageRestrict, s);
   mark(kStageLattice);
@@ -3671,7 +3710,6 @@ hipError_t launch_eval(int mode, const LaunchGeom& L, hipStream_t s, const Io& i
     for (int k = L.max_levels - 2; k >= 0; --k) {
       const int nb = L.prolong_level[k].blocks;
       if (nb == 0) continue;
-      ghosts(k + 1, kGhostU, 0);
       const KArgs A = args(L.prolong_level[k]);
       if (L.order == 4)
         k_prolong<4, true><<<nb, kPThreads, lds, s>>>(A, k);
@@ -3690,7 +3728,6 @@ hipError_t launch_eval(int mode, const LaunchGeom& L, hipStream_t s, const Io& i
       k_prolong<6, false><<<L.prolong.blocks, kPThreads, lds, s>>>(args(L.prolong), 0);
     }
   }
-  ghosts(0, kGhostU, 0);
   end(kStageProlong, s);
   mark(kStageInterp);
   if (short_side) join(cc->shortr);
