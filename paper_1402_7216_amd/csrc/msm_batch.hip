@@ -118,6 +118,7 @@ void rebuild_maps(msm_batch* Bt) {
   L.short_split = Bt->plans[0]->short_split;
   L.lat_b = 0;
   L.bin4 = false;
+  L.binr_chunk = Bt->plans[0]->g.binr_chunk;       // (the same for every system of a batch)
   for (int st = 0; st < kNumStages; ++st) Bt->map[st].clear();
   for (int s = 0; s < Bt->n_sys; ++s) {
     const msm_plan* P = Bt->plans[s];

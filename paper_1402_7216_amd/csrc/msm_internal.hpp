@@ -27,7 +27,9 @@ constexpr int kXSub = 4;                  // link cells are this many times fine
 constexpr int kBinMaxCells = 8192;        // cells the two-kernel binning keeps in LDS
 constexpr int kBinMaxHist = 1 << 20;      // block histogram entries of the two-kernel binning
 constexpr int kBinRowAtoms = 32768;       // atoms per system at most for the one-kernel binning
-constexpr int kBinRChunk = 8192;          // atoms per block of the row binning's count and scatter
+constexpr int kBinRChunk = 8192;          // atoms per block of the row binning's count and scatter, at most
+constexpr int kBinRMinChunk = 1024;       // and at least
+constexpr int kBinRBlocks = 128;          // blocks up to which the chunk is kept small
 constexpr int kBinRowsMax = 8192;         // cell rows of a system at most for the row binning
 constexpr int kBinRSortCap = 1024;        // atoms of a cell row the row binning's sort keeps in LDS
 constexpr int kBinRowCells = 512;         // cells one block of the one-kernel binning owns at most
@@ -78,7 +80,8 @@ struct Geom {
   int max_cells;                   // cells of the finest reach any tuning may select (sizes the cell arrays)
   int bin_blocks;                  // blocks of the two-kernel binning (0: another binning)
   int bin_row_blocks;              // blocks of the one-kernel binning (0: another binning)
-  int binr_blocks;                 // blocks (kBinRChunk atoms each) of the row binning (0: another binning)
+  int binr_blocks;                 // blocks (binr_chunk atoms each) of the row binning (0: another binning)
+  int binr_chunk;
   int reach;                       // neighbour cell rows per side in y and z
   float inv_cs[3];                 // 1 / cell edge
   float cs[3];                     // cell edge (x cells are kXSub times finer than y, z)
@@ -349,6 +352,7 @@ struct LaunchGeom {
   StageGrid rchunk;                  // row binning: count and scatter (systems with binr_blocks > 0)
   StageGrid rscan;                   // row binning: one block per system
   StageGrid rsort;                   // row binning: one block per cell row
+  int binr_chunk = kBinRChunk;       // atoms per block of the row binning (one for the launch)
   int rsort_lds = 0;                 // dynamic LDS of the row binning's sort (largest system)
   bool periodic = false;             // periodic grids: the level-0 charges of the images are folded in
   bool short_periodic = false;       // periodic short range (MSM or pair plans)

@@ -837,7 +837,7 @@ __global__ void __launch_bounds__(kBRThreads) k_bin_rows(KArgs A) {
 // Link cells of a large system in four kernels, by cell row first: the cells
 // are numbered (cz ny + cy) nx + cx, so a cell row r = cz ny + cy is a
 // contiguous range of cells.
-//   k_binr_count   per block of kBinRChunk atoms: LDS counts of the rows, one
+//   k_binr_count   per block of binr_chunk atoms: LDS counts of the rows, one
 //                  global add per row into counts[]
 //   k_binr_scan    row starts (exclusive scan of counts[]); clears counts[]
 //                  and the row cursors for the scatter and the next call
@@ -850,7 +850,6 @@ __global__ void __launch_bounds__(kBRThreads) k_bin_rows(KArgs A) {
 // The row starts live in the scan array.
 // --------------------------------------------------------------------------
 constexpr int kBRCThreads = 1024;
-constexpr int kBRCPer = kBinRChunk / kBRCThreads;
 constexpr int kBRSThreads = 256;
 static_assert(kBinRSortCap % kBRSThreads == 0 && kBinRSortCap <= kRankCap, "a cached row ranks every cell");
 static_assert(kBinRSortCap <= 65536 && kBinRowsMax <= 65536, "16-bit x cells and positions");
@@ -893,6 +892,12 @@ __device__ int block_exclusive_scan(int* a, int n, int* wsum) {
   return total;
 }
 
+// PER: atoms per thread (g.binr_chunk = PER kBRCThreads).  Few blocks are
+// bound by their chain of loads, atomics and stores, many by the rows' atomics:
+// chunks of 1,024 atoms up to 128 blocks, then larger ones (50,000 atoms,
+// chunks of 8,192 and 1,024: scatter 9.5 and 4.7 us; 100,000: 10.6 and 5.8;
+// 1,000,000, chunks of 8,192 and 4,096: 15.2 and 17.6).
+template <int PER>
 __global__ void __launch_bounds__(kBRCThreads) k_binr_count(KArgs A) {
   int blk;
   const SysDesc& S = sys_of(A, blk);
@@ -904,16 +909,16 @@ __global__ void __launch_bounds__(kBRCThreads) k_binr_count(KArgs A) {
   __syncthreads();
   const float* y = A.io.y + S.atom_off;
   const float* z = A.io.z + S.atom_off;
-  const int i0 = blk * kBinRChunk;
-  float py[kBRCPer], pz[kBRCPer];
+  const int i0 = blk * (PER * kBRCThreads);
+  float py[PER], pz[PER];
 #pragma unroll
-  for (int u = 0; u < kBRCPer; ++u) {
+  for (int u = 0; u < PER; ++u) {
     const int i = i0 + u * kBRCThreads + threadIdx.x;
     py[u] = i < g.n_atoms ? y[i] : 0.f;
     pz[u] = i < g.n_atoms ? z[i] : 0.f;
   }
 #pragma unroll
-  for (int u = 0; u < kBRCPer; ++u)
+  for (int u = 0; u < PER; ++u)
     if (i0 + u * kBRCThreads + (int)threadIdx.x < g.n_atoms) atomicAdd(&hist[cell_row(g, py[u], pz[u])], 1);
   __syncthreads();
   int* __restrict__ counts = S.d.counts;
@@ -949,6 +954,7 @@ __global__ void __launch_bounds__(kBRCThreads) k_binr_scan(KArgs A) {
   }
 }
 
+template <int PER>
 __global__ void __launch_bounds__(kBRCThreads) k_binr_scatter(KArgs A) {
   int blk;
   const SysDesc& S = sys_of(A, blk);
@@ -963,16 +969,16 @@ __global__ void __launch_bounds__(kBRCThreads) k_binr_scatter(KArgs A) {
   const float* y = A.io.y + S.atom_off;
   const float* z = A.io.z + S.atom_off;
   const float* q = A.io.q + S.atom_off;
-  const int i0 = blk * kBinRChunk;
-  float4 p[kBRCPer];
-  int rr[kBRCPer];
+  const int i0 = blk * (PER * kBRCThreads);
+  float4 p[PER];
+  int rr[PER];
 #pragma unroll
-  for (int u = 0; u < kBRCPer; ++u) {
+  for (int u = 0; u < PER; ++u) {
     const int i = i0 + u * kBRCThreads + threadIdx.x;
     p[u] = i < g.n_atoms ? make_float4(x[i], y[i], z[i], q[i]) : make_float4(0.f, 0.f, 0.f, 0.f);
   }
 #pragma unroll
-  for (int u = 0; u < kBRCPer; ++u) {
+  for (int u = 0; u < PER; ++u) {
     const int i = i0 + u * kBRCThreads + threadIdx.x;
     rr[u] = -1;
     if (i < g.n_atoms) {
@@ -993,7 +999,7 @@ __global__ void __launch_bounds__(kBRCThreads) k_binr_scatter(KArgs A) {
   int* __restrict__ tmp = S.d.tmp;
   float4* __restrict__ tmp4 = S.d.fshort;   // coordinate copies until k_binr_sort
 #pragma unroll
-  for (int u = 0; u < kBRCPer; ++u)
+  for (int u = 0; u < PER; ++u)
     if (rr[u] >= 0) {
       const int slot = base[rr[u]] + atomicAdd(&hist[rr[u]], 1);
       if ((unsigned)slot < (unsigned)n) {                 // only a corrupted workspace fails this
@@ -3515,9 +3521,19 @@ hipError_t launch_eval(int mode, const LaunchGeom& L, hipStream_t s, const Io& i
     k_bin_rows<<<L.binrow.blocks, kBRThreads, L.binrow_lds, s>>>(args(L.binrow));
   }
   if (L.rchunk.blocks > 0) {
-    k_binr_count<<<L.rchunk.blocks, kBRCThreads, 0, s>>>(args(L.rchunk));
-    k_binr_scan<<<L.rscan.blocks, kBRCThreads, 0, s>>>(args(L.rscan));
-    k_binr_scatter<<<L.rchunk.blocks, kBRCThreads, 0, s>>>(args(L.rchunk));
+#define MSM_BINR(PER)                                                             \
+  do {                                                                            \
+    k_binr_count<PER><<<L.rchunk.blocks, kBRCThreads, 0, s>>>(args(L.rchunk));    \
+    k_binr_scan<<<L.rscan.blocks, kBRCThreads, 0, s>>>(args(L.rscan));            \
+    k_binr_scatter<PER><<<L.rchunk.blocks, kBRCThreads, 0, s>>>(args(L.rchunk));  \
+  } while (0)
+    switch (L.binr_chunk / kBRCThreads) {
+      case 1: MSM_BINR(1); break;
+      case 2: MSM_BINR(2); break;
+      case 4: MSM_BINR(4); break;
+      default: MSM_BINR(8); break;
+    }
+#undef MSM_BINR
     (void)hipFuncSetAttribute((const void*)k_binr_sort, hipFuncAttributeMaxDynamicSharedMemorySize, L.rsort_lds);
     k_binr_sort<<<L.rsort.blocks, kBRSThreads, L.rsort_lds, s>>>(args(L.rsort));
   }
