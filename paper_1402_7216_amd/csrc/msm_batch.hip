@@ -581,7 +581,16 @@ static msm_status autotune(bool batch, void* obj, void* ws, size_t ws_bytes, msm
   hipEvent_t e0 = nullptr, e1 = nullptr;
   hipError_t he = hipEventCreate(&e0);
   if (he == hipSuccess) he = hipEventCreate(&e1);
-  if (he != hipSuccess) return hip_fail(he, "create timing events");
+  // the timed evaluations return an energy: without one (and potentials) they
+  // would run the short range that sums forces alone
+  double* energy = nullptr;
+  if (he == hipSuccess)
+    he = hipMalloc((void**)&energy, sizeof(double) * (size_t)(batch ? static_cast<msm_batch*>(obj)->n_sys : 1));
+  if (he != hipSuccess) {
+    if (e0) (void)hipEventDestroy(e0);
+    if (e1) (void)hipEventDestroy(e1);
+    return hip_fail(he, "create timing events and energy output");
+  }
   msm_batch* Bt = batch ? static_cast<msm_batch*>(obj) : nullptr;
   msm_plan* P = batch ? nullptr : static_cast<msm_plan*>(obj);
   const bool tiled = batch ? Bt->lg.lat_b > 0 : P->lat.b > 0;
@@ -590,9 +599,9 @@ static msm_status autotune(bool batch, void* obj, void* ws, size_t ws_bytes, msm
   };
   auto eval = [&]() {
     return batch ? msm_batch_compute(Bt, ws, ws_bytes, stream, x, y, z, q, nullptr, nullptr, nullptr, nullptr,
-                                     nullptr, nullptr)
+                                     energy, nullptr)
                  : msm_compute(P, ws, ws_bytes, stream, x, y, z, q, nullptr, nullptr, nullptr, nullptr,
-                               nullptr, nullptr);
+                               energy, nullptr);
   };
   auto describe = [](const msm_tuning& t) {
     return "\"lattice_b\": " + std::to_string(t.lattice_b) + ", \"item_chunks\": " + std::to_string(t.item_chunks) +
@@ -703,6 +712,7 @@ static msm_status autotune(bool batch, void* obj, void* ws, size_t ws_bytes, msm
   }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
+  (void)hipFree(energy);
   if (st != MSM_OK) return st;
   st = tune(bt);
   if (st != MSM_OK) return st;
