@@ -17,6 +17,7 @@ constexpr int kShortParts = 4;           // parts a small system sums a wave's r
 constexpr int kShortSmallItems = 256;    // short-range work items up to which a system is small (one block per CU)
 constexpr int kAntTiles = 512;           // anterpolation tiles of a system, at least (where the grid has the nodes)
 constexpr int kAntBatchTiles = 1024;     // tiles of a batch, shared by its systems
+constexpr int kShortLaterBlocks = 1024;  // short-range blocks up to which it is enqueued after the restriction
 constexpr int kLattice0SideBlocks = 1024; // level-0 lattice blocks from which that launch gets a stream of its own
 constexpr int kShortRowsPerWave = 24;    // neighbour rows one wave can take
 constexpr int kMaxOrder = 6;
