@@ -12,6 +12,7 @@
 // Every per-atom and per-node value is a gather in a fixed order, so results
 // are bitwise reproducible.  All arithmetic is float32 except the top-level
 // sum and the energy / virial reductions (float64).
+#include "msm_index.hpp"
 #include "msm_internal.hpp"
 
 namespace msm {
@@ -32,17 +33,6 @@ __device__ __forceinline__ const SysDesc& stage_desc(const SysDesc& src, SysDesc
   for (int i = threadIdx.x; i < (int)(sizeof(SysDesc) / 16); i += blockDim.x) d4[i] = s4[i];
   __syncthreads();
   return *dst;
-}
-
-// Quotient and remainder of 0 <= i < 2^20 by 0 < d <= 2^10 with a float
-// reciprocal (inv_d = 1/d rounded): (i + 1/2)/d lies at least 1/(2d) away from
-// an integer, far more than the rounding error of (i + 1/2) * inv_d, so the
-// truncation is exact.  Replaces the long integer-division sequence for
-// runtime divisors in index arithmetic.
-__device__ __forceinline__ int fdiv(int i, int d, float inv_d, int& rem) {
-  const int q = (int)(((float)i + 0.5f) * inv_d);
-  rem = i - q * d;
-  return q;
 }
 
 // --------------------------------------------------------------------------
@@ -1950,9 +1940,8 @@ __global__ void __launch_bounds__(kBlock) k_anterp_gather(KArgs A) {
   const Level L = g.lv[0];
   const int node = blk * kBlock + threadIdx.x;
   if (node >= L.count) return;
-  const float inv_n0 = 1.f / (float)L.n[0], inv_n1 = 1.f / (float)L.n[1];
   int m[3];
-  m[2] = fdiv(fdiv(node, L.n[0], inv_n0, m[0]), L.n[1], inv_n1, m[1]);
+  node_position(node, L.n, L.count, m);
   int t0[3], t1[3];
   bool any = true;
 #pragma unroll
@@ -1992,18 +1981,6 @@ __global__ void __launch_bounds__(kBlock) k_anterp_gather(KArgs A) {
 // about 4 us, and an evaluation had one after every stage (9,000 atoms: seven,
 // 27 of 163 us of kernels and as many gaps; 127 us an evaluation, 122 without).
 // --------------------------------------------------------------------------
-// The images of a node i of the period [0, p) along one dimension, itself
-// included: i + j p for j = first .. first + count - 1, those in [-G, p + G).
-struct ImageRange {
-  int first, count;
-};
-__device__ __forceinline__ ImageRange image_range(int i, int p, int G) {
-  const float inv_p = 1.f / (float)p;
-  int rem;
-  const int below = fdiv(i + G, p, inv_p, rem), above = fdiv(p + G - 1 - i, p, inv_p, rem);
-  return {-below, below + above + 1};
-}
-
 // f(offset) for the node (ix, iy, iz) of the period, then for every image of
 // it among the level's nodes [-G, period + G).  Several threads may share the
 // images of a node: this one takes image `sub` and every `step`-th after it
@@ -2258,13 +2235,12 @@ __global__ void __launch_bounds__(kBlock) k_fold(KArgs A) {
   const int node = (int)blockIdx.x * kBlock + (int)threadIdx.x;
   if (node >= L.count) return;
   const int G = g.ghost;
-  const float inv_n0 = 1.f / (float)L.n[0], inv_n1 = 1.f / (float)L.n[1];
-  int mx, my;
-  const int mz = fdiv(fdiv(node, L.n[0], inv_n0, mx), L.n[1], inv_n1, my);
-  auto wrap = [G](int m, int p) { const int i = (m - G) % p; return i < 0 ? i + p : i; };
+  int m[3];
+  node_position(node, L.n, L.count, m);
+  auto wrap = [G](int i, int p) { const int r = (i - G) % p; return r < 0 ? r + p : r; };
   const float* __restrict__ raw = S.d.u + L.off;
   float v = 0.f;
-  each_image(L, G, wrap(mx, L.per[0]), wrap(my, L.per[1]), wrap(mz, L.per[2]), [&](int at) { v += raw[at]; });
+  each_image(L, G, wrap(m[0], L.per[0]), wrap(m[1], L.per[1]), wrap(m[2], L.per[2]), [&](int at) { v += raw[at]; });
   S.d.qgrid[L.off + node] = v;
 }
 
