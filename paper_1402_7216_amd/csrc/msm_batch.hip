@@ -285,11 +285,13 @@ msm_status msm_batch_create(const msm_params* params, const int32_t* n_atoms, in
       return fail(MSM_ERR_UNSUPPORTED, "mixed stencil widths in one batch");
     }
   }
-  // common lattice template: the largest system's choice
-  int big = 0;
-  for (int s = 1; s < n_sys; ++s)
-    if (n_atoms[s] > n_atoms[big]) big = s;
-  const int b0 = Bt->plans[big]->lat.b;
+  // common lattice template: the choice of the largest system that has one (a
+  // system of one level has no lattice cutoff).  One launch serves them all, so
+  // every system's tiles and window must be those of that template
+  int big = -1;
+  for (int s = 0; s < n_sys; ++s)
+    if (Bt->plans[s]->lat.b > 0 && (big < 0 || n_atoms[s] > n_atoms[big])) big = s;
+  const int b0 = big < 0 ? 0 : Bt->plans[big]->lat.b;
   for (msm_plan* P : Bt->plans) retune(P, msm_tuning{b0, 0, 0, 0, 0, 0, 0, 0});
 
   // stage-table reserves: the most blocks any tuning can ask for
