@@ -152,23 +152,18 @@ size_t align256(size_t v) { return (v + 255) & ~size_t(255); }
 
 bool finite_pos(double v) { return std::isfinite(v) && v > 0.0; }
 
-// Bits of the float16 nearest to v (ties to even; |v| below 65,520).
-uint16_t half_bits(double v) {
-  const uint16_t sign = std::signbit(v) ? 0x8000 : 0;
-  const double a = std::fabs(v);
-  if (a == 0.0) return sign;
+// The bfloat16 (8 significant bits) nearest to v, and its bits.
+double bf16_nearest(double v) {
   int e = 0;
-  (void)std::frexp(a, &e);                                 // a in [2^(e-1), 2^e)
-  const int unit = std::max(e - 11, -24);                  // exponent of the last place
-  const int m = (int)std::nearbyint(std::ldexp(a, -unit)); // 11 bits at most, or 2^11 after rounding up
-  if (unit == -24) return (uint16_t)(sign | m);            // subnormal (2^10 becomes the smallest normal)
-  return (uint16_t)(sign | (((unit + 24) << 10) + m));     // the leading bit carries into the exponent
+  (void)std::frexp(v, &e);                                 // |v| in [2^(e-1), 2^e)
+  return std::ldexp(std::nearbyint(std::ldexp(v, 8 - e)), e - 8);
 }
 
-double half_value(uint16_t h) {
-  const int e = (h >> 10) & 31, m = h & 1023;
-  const double v = e ? std::ldexp(1024.0 + m, e - 25) : std::ldexp((double)m, -24);
-  return (h & 0x8000) ? -v : v;
+uint16_t bf16_bits(double nearest) {
+  const float f = (float)nearest;
+  uint32_t u;
+  std::memcpy(&u, &f, sizeof u);
+  return (uint16_t)(u >> 16);
 }
 
 // Weight fragments of the tiled lattice-cutoff kernel for the taps W(|n|),
@@ -180,17 +175,10 @@ double half_value(uint16_t h) {
 template <class Weight>
 void lattice_fragments(int H, double rad, Weight weight, msm::LatLaunch& lat, std::vector<uint16_t>& frags) {
   auto inside = [&](int n2) { return std::sqrt((double)n2) < rad; };
-  double wmax = 0.0;
   for (int n2 = 0; n2 <= 3 * H * H; ++n2)
-    if (inside(n2)) {
-      wmax = std::max(wmax, std::fabs(weight(n2)));
-      lat.n2max = n2;
-    }
-  int e = 0;
-  (void)std::frexp(wmax, &e);
-  lat.wexp = 14 - e;                                       // the largest weight lands in [2^13, 2^14)
+    if (inside(n2)) lat.n2max = n2;
   lat.phases = (2 * H + msm::kLatPlanes) / msm::kLatPlanes;
-  const int words = msm::kLatFragBytes / 2, half = words / 2;
+  const int words = msm::kLatFragBytes / 2, part = words / 3;
   const int n_main = (H + msm::kLatPlanes) * (H + 1), n_wing = H > 8 ? 2 * lat.phases * (H + 1) : 0;
   frags.assign((size_t)(n_main + n_wing) * words, 0);
   auto octet = [&](int id, int quad, int first, int ay, int az) {
@@ -199,10 +187,12 @@ void lattice_fragments(int H, double rad, Weight weight, msm::LatLaunch& lat, st
       for (int i = 0; i < 8; ++i) {
         const int nx = first + i - (l & 15), n2 = nx * nx + ay * ay + az * az;
         if (std::abs(nx) > H || !inside(n2)) continue;
-        const double w = std::ldexp(weight(n2), lat.wexp);
-        const uint16_t hi = half_bits(w);
-        frags[(size_t)id * words + l * 8 + i] = hi;
-        frags[(size_t)id * words + half + l * 8 + i] = half_bits(w - half_value(hi));
+        double w = ay ? weight(n2) : 0.5 * weight(n2);     // (the pair +-0 counts its row twice)
+        for (int p = 0; p < 3; ++p) {
+          const double near = bf16_nearest(w);
+          frags[(size_t)id * words + p * part + l * 8 + i] = bf16_bits(near);
+          w -= near;
+        }
       }
   };
   for (int az = 0; az <= H; ++az)                          // (the last phase's planes beyond H stay zero)
@@ -223,7 +213,7 @@ int lattice_row(const msm::LatLaunch& lat, int ph, int ay) {
   return n2 > lat.n2max ? 0 : (lat.H > 8 && 81 + n2 <= lat.n2max ? 2 : 1);
 }
 
-// Cuts the rows of a phase into contiguous shares of 4 waves with the least
+// Cuts the row pairs of a phase into contiguous shares of 4 waves with the least
 // largest cost, which it returns (fragment pairs; wings count half).
 double cut_rows(msm::LatLaunch& lat, int ph) {
   constexpr int waves = 4;
@@ -231,7 +221,7 @@ double cut_rows(msm::LatLaunch& lat, int ph) {
   for (int ay = 0; ay <= lat.H; ++ay) {
     const int kind = lattice_row(lat, ph, ay);
     if (kind == 0) break;
-    for (int sgn = 0; sgn < (ay ? 2 : 1); ++sgn) cost.push_back(kind == 2 ? 1.5 : 1.0);
+    cost.push_back(kind == 2 ? 1.5 : 1.0);
   }
   auto shares = [&](double cap, unsigned char* cut) {
     int w = 0;
@@ -259,20 +249,25 @@ double cut_rows(msm::LatLaunch& lat, int ph) {
   return hi;
 }
 
-// Tiles of the lattice-cutoff kernel: planes per block (force_b, or by the
-// rule below), the phases' rows cut into the waves' shares, and the split of
-// each level's phases over blocks: more blocks fill the chip, fewer write and
-// read back fewer partials.  The estimate in cycles: a block starts and ends
-// (9,000), each phase stages its window and runs its rows on the matrix pipe,
-// 48 cycles a fragment pair; the work is spread over the blocks that fit the
-// 256 compute units, plus the longest block.  100,000-atom box, level 0 in 1, 2,
-// 3, 5 blocks per tile: 78, 47, 43, 44 us; 1M box in 1, 2, 3, 5: 105, 116, 111, 115.
+// Tiles of the lattice-cutoff kernel: planes per block (force_b, or 4: two
+// blocks fit a CU, so one stages its window while the other multiplies), the
+// phases' rows cut into the waves' shares, and the split of each level's phases
+// over blocks: more blocks fill the chip, fewer write and read back fewer
+// partials.  The coarse levels' blocks come last and are split as far as they
+// can be.  Level 0 by an estimate in cycles: a block starts and ends (9,000),
+// each phase stages its window and runs its rows on the matrix pipe, 96 cycles a
+// fragment pair and plane; the work is spread over the blocks that fit the 256
+// compute units, plus the longest block.
+// Stage time with 4, 6 and 8 planes: 1,000 charges 10.6, 12.4, 12.8 us; 9,000
+// periodic 24.2, 24.2, 26.1; 24,000 atoms 31, 35, 36; 1M 113, 145, 132; 1M
+// periodic 58, 75, 66.  Level 0 in 1, 2, 3, 6 blocks a tile: 24,000 atoms 57, 35,
+// 29, 31 us; 100,000 atoms 81, 55, 54, 56 (68 with the coarse levels in 5 and 3
+// blocks); 1M in 1, 2, 3, 5: 112, 129, 119, 124.
 void choose_lattice_tiles(const Geom& g, int H_, msm::LatLaunch& lat, int force_b = 0) {
-  const int phases = lat.phases, wexp = lat.wexp, n2max = lat.n2max;
+  const int phases = lat.phases, n2max = lat.n2max;
   std::memset(&lat, 0, sizeof(lat));
   lat.H = H_;
   lat.phases = phases;
-  lat.wexp = wexp;
   lat.n2max = n2max;
   if (g.levels < 2 || H_ > msm::kLatMaxHalo) return;
   const int skip = g.periodic ? g.ghost : 0;
@@ -285,19 +280,14 @@ void choose_lattice_tiles(const Geom& g, int H_, msm::LatLaunch& lat, int force_
     t.ntz = (L.n[2] - 2 * skip + B - 1) / B;
     return (double)t.ntx * t.nty * t.ntz;
   };
-  // 6 planes unless that leaves the chip mostly empty (fewer than 128 blocks on
-  // level 0), where 4 fill it better: 24,000-atom box (324 blocks) 28.8 us with
-  // 4, 23.1 with 6, 32.4 with 8 planes; 9,000-atom periodic box (96 blocks)
-  // 22.5, 24.3 and 24.4; 1,000 charges (8 blocks) 11.6, 12.4 and 13.4
-  msm::LatTile probe{};
-  const int B = force_b ? force_b : (tiles_of(0, 6, probe) * phases < 128.0 ? 4 : 6);
+  const int B = force_b ? force_b : 4;
   lat.b = B;
   lat.n = g.levels - 1;
   lat.lds_bytes = msm::lat_lds(H_, B);
   std::vector<double> mat(phases);                         // fragment pairs of each phase's slowest wave
   for (int ph = 0; ph < phases; ++ph) mat[ph] = cut_rows(lat, ph);
   // blocks on the chip at a time (two on a CU share its matrix pipes)
-  const int slots = 256 * (B < 8 && 2 * (lat.lds_bytes + 4096) <= 160 * 1024 ? 2 : 1);
+  const int slots = 256 * (B == 4 && 2 * (lat.lds_bytes + 2048) <= 160 * 1024 ? 2 : 1);
   int blocks = 0;
   for (int k = 0; k < g.levels - 1; ++k) {
     const msm::Level& L = g.lv[k];
@@ -311,11 +301,11 @@ void choose_lattice_tiles(const Geom& g, int H_, msm::LatLaunch& lat, int force_
       for (int q = 0; q < G; ++q) {
         double blk = 9000.0;
         for (int ph = phases * q / G; ph < phases * (q + 1) / G; ++ph)
-          blk += 3000.0 + 500.0 * (B + 3) + mat[ph] * 48.0 * msm::kLatPlanes * B * (slots / 256);
+          blk += 3000.0 + 500.0 * (B + 3) + mat[ph] * 96.0 * msm::kLatPlanes * B * 4 / msm::lat_waves(B);
         sum += blk;
         longest = std::max(longest, blk);
       }
-      const double est = tiles * sum / slots + longest + (G > 1 ? 0.013 * G * L.count : 0.0);
+      const double est = k > 0 ? -G : tiles * sum / slots + longest + (G > 1 ? 0.013 * G * L.count : 0.0);
       if (est < best) {
         best = est;
         t.groups = G;
@@ -463,6 +453,7 @@ void refresh_launch(msm_plan* P) {
   lg.short_split_rows = g.short_parts > 1;
   lg.anterp.blocks = sb.anterp;
   lg.lattice0.blocks = sb.lattice0;
+  lg.lattice0_tiles = msm::lattice0_tiles(P->lat);
   lg.lattice.blocks = sb.lattice;
   lg.lattice_all.blocks = sb.lattice_all;
   lg.top.blocks = sb.top;
@@ -665,12 +656,12 @@ void set_anterp_tiles(Geom& g, int target) {
 //    stream is right for them too (74 us against 77 and 84), and periodic ones
 //    take it always: their grid stages have twice the launches for the short
 //    range to hide behind (9,000 atoms: 139 us, 151 in order).
-//  - The level-0 lattice cutoff beside the coarse levels pays from about 1,000
-//    blocks (1,000,000 atoms, 1152 blocks: 1119 us, 1128 without; 100,000 atoms,
-//    864 blocks: 420 and 421; 50,000, 315 blocks: 622 and 616; 24,000, 324
-//    blocks: 112 and 106 as a graph).
+//  - The level-0 lattice cutoff beside the coarse levels costs nothing from
+//    about 500 tiles and pays in batches (64 systems as a graph 1402 us, 1416
+//    without; 16 systems 425 and 426; 1,000,000 atoms, 828 tiles: 1135 and 1131;
+//    100,000, 224 tiles: 412 and 407; 24,000, 81 tiles: 145 and 107 as a graph).
 void default_streams(msm::LaunchGeom& L, bool periodic) {
-  L.streams = L.lattice0.blocks >= msm::kLattice0SideBlocks && !periodic ? 3 : 2;
+  L.streams = L.lattice0_tiles >= msm::kLattice0SideTiles && !periodic ? 3 : 2;
   L.capture_streams = L.streams;
   if (L.short_parts > 1 && !periodic) L.streams = 1;
 }

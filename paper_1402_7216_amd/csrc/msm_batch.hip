@@ -148,7 +148,9 @@ void rebuild_maps(msm_batch* Bt) {
   // systems that split their rows; else a wave takes all parts of its rows
   L.short_parts = L.shortr.blocks <= 2 * msm::kShortSmallItems ? msm::kShortParts : 1;
   L.streams = L.capture_streams = Bt->plans[0]->streams;
+  L.lattice0_tiles = 0;
   for (const msm_plan* P : Bt->plans) {
+    L.lattice0_tiles += msm::lattice0_tiles(P->lat);
     L.short_parts = std::min(L.short_parts, P->g.short_parts);
     L.short_split_rows |= P->g.short_parts > 1;
   }

@@ -18,7 +18,7 @@ constexpr int kShortSmallItems = 256;    // short-range work items up to which a
 constexpr int kAntTiles = 512;           // anterpolation tiles of a system, at least (where the grid has the nodes)
 constexpr int kAntBatchTiles = 1024;     // tiles of a batch, shared by its systems
 constexpr int kShortLaterBlocks = 1024;  // short-range blocks up to which it is enqueued after the restriction
-constexpr int kLattice0SideBlocks = 1024; // level-0 lattice blocks from which that launch gets a stream of its own
+constexpr int kLattice0SideTiles = 500;  // level-0 lattice tiles from which that launch gets a stream of its own
 constexpr int kShortRowsPerWave = 24;    // neighbour rows one wave can take
 constexpr int kMaxOrder = 6;
 constexpr int kMaxTopNodes = 1 << 17;     // all-pairs FP64 top level stays below ~1e10 pair terms
@@ -105,7 +105,7 @@ struct Geom {
   float dr[8];                     // 2 k c_k / a^(2k+1)   (gamma'(r/a)/(a^2 r) = sum_{k>=1} dr[k] r^2(k-1))
   int at[3];                       // anterpolation node tile (level-0 nodes per dimension)
   int atn[3];                      // anterpolation tiles per dimension (they own floor indices 0..fmax)
-  long long part_cap;              // float32 partials the lattice cutoff's phase groups may use
+  long long part_cap;              // float64 partials the lattice cutoff's phase groups may use
   int at_ext;                      // nodes of a tile's private region (at[d] + order - 1 per dimension)
   int pair;                        // 0: MSM; else the cheap pair method evaluated alone (kPair*)
   float pk[4];                     // constants of the pair method (see k_short)
@@ -138,12 +138,12 @@ struct LatTile {
 
 constexpr int kLatMaxHalo = 13;          // tiled kernel handles stencil half-widths up to this
 constexpr int kLatPlanes = 4;            // stencil planes per phase
-// Waves per block: 4 for up to 6 planes (two blocks per CU where the window
-// allows), two groups of 4 for 8 planes, whose window leaves room for one block.
-__host__ __device__ constexpr int lat_waves(int b) { return b == 8 ? 8 : 4; }
+// Waves per block: 4 for 4 planes (two blocks per CU where the window allows),
+// two groups of 4 for 6 and 8 planes, whose window leaves room for one block.
+__host__ __device__ constexpr int lat_waves(int b) { return b == 4 ? 4 : 8; }
 constexpr int kLatMaxPhases = (2 * kLatMaxHalo + kLatPlanes) / kLatPlanes;
 constexpr int kLatMaxGroups = 8;         // phase groups per tile
-constexpr int kLatFragBytes = 2048;      // weight fragment: float16 high and low parts of 16 x 32 weights
+constexpr int kLatFragBytes = 3072;      // weight fragment: the three bfloat16 parts of 16 x 32 weights
 
 struct LatLaunch {
   int b;                   // z planes per block (template), 0 = use the untiled kernel
@@ -151,24 +151,24 @@ struct LatLaunch {
   int H;                   // stencil half-width in nodes
   int lds_bytes;           // dynamic LDS per block
   int phases;              // groups of kLatPlanes stencil planes
-  int wexp;                // weights are stored times 2^wexp
   int n2max;               // largest |n|^2 of a tap
   int n_part;              // float64 partials of every grouped level
-  // row i of a phase is ny = 0 (i = 0), (i + 1) / 2 (odd i) or -(i + 1) / 2;
-  // wave w of a group of 4 takes rows cut[phase][w] .. cut[phase][w + 1] - 1
+  // wave w of a group of 4 takes the row pairs ny = +-cut[phase][w] .. cut[phase][w + 1] - 1
   unsigned char cut[kLatMaxPhases][8];
   LatTile t[kMaxLevels];
 };
 
+inline int lattice0_tiles(const LatLaunch& P) { return P.b > 0 && P.n > 0 ? P.t[0].ntx * P.t[0].nty * P.t[0].ntz : 0; }
+
 // Input window of one phase of a tile: octets (8 x values) per row, row pitch
-// in values (an odd multiple of 8: the 16 rows of a fragment then start in
+// in floats (an odd multiple of 4: the 16 rows of a fragment then start in
 // distinct LDS bank groups) and rows; one octet of every row per thread.
 __host__ __device__ inline int lat_left(int H) { return H > 8 ? 2 : 1; }            // octets left of the tile
 __host__ __device__ inline int lat_octets(int H) { return 2 + 2 * lat_left(H); }
-__host__ __device__ inline int lat_pitch(int H) { return 8 * lat_octets(H) + 8; }
+__host__ __device__ inline int lat_pitch(int H) { return 8 * lat_octets(H) + 4; }
 __host__ __device__ inline int lat_rows(int H) { return 16 + 2 * H; }
 static_assert((16 + 2 * kLatMaxHalo) * 6 <= 256, "a thread (of 256) per octet of a plane");
-// high and low halves of the window, or the waves' float64 totals
+// the window, or the waves' float64 totals
 __host__ __device__ inline int lat_lds(int H, int b) {
   const int win = (b + kLatPlanes - 1) * lat_rows(H) * lat_pitch(H) * 4, red = 4 * 64 * 4 * b * 8;
   return win > red ? win : red;
@@ -194,7 +194,7 @@ enum Section : int {
                       // double[]: phase-group partials of the lattice cutoff
   kSecRows,           // StencilRow[n_rows]
   kSecWeights,        // float[n_weights]
-  kSecLatFrags,       // float16 weight fragments of the tiled lattice kernel
+  kSecLatFrags,       // bfloat16 weight fragments of the tiled lattice kernel
   kSecTop,            // double[top table]
   kSecPartials,       // double[10 * n_partials]: energy, then 9 virial components
   kSecDesc,           // SysDesc: this workspace's descriptor (pointers into it)
@@ -331,7 +331,7 @@ struct LaunchGeom {
   int order = 4;                     // common to every system of a launch
   int m = 2;
   int pair = kPairMsm;               // pair method (common to every system of a launch)
-  int lat_b = 0;                     // z planes per wave of the tiled lattice kernel, 0 = untiled kernel
+  int lat_b = 0;                     // z planes per block of the tiled lattice kernel, 0 = untiled kernel
   int lat_lds = 0;                   // dynamic LDS of the tiled kernel
   int max_levels = 1;
   int streams = 3;                   // 1: in order; 2: short range on a side stream; 3: also level-0 lattice
@@ -360,6 +360,7 @@ struct LaunchGeom {
   int binrow_lds = 0;                // dynamic LDS of the one-kernel binning (largest system)
   bool bin4 = true;                  // some system uses the four-kernel binning
   StageGrid lattice0;                // lattice cutoff of level 0
+  int lattice0_tiles = 0;            // its tiles, of every system
   StageGrid lattice;                 // lattice cutoff of levels 1 .. l-2 (with the top level)
   StageGrid lattice_all;             // every level in one launch (no level-0 side stream)
   StageGrid restrict_[kMaxLevels];   // level k -> k+1

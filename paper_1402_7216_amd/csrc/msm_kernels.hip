@@ -11,7 +11,9 @@
 //
 // Every per-atom and per-node value is a gather in a fixed order, so results
 // are bitwise reproducible.  All arithmetic is float32 except the top-level
-// sum and the energy / virial reductions (float64).
+// sum, the totals of the lattice cutoff and the energy / virial reductions
+// (float64), the charges' 64-bit fixed-point sums, and the lattice cutoff's
+// products (float32 numbers in three bfloat16 parts).
 #include "msm_index.hpp"
 #include "msm_internal.hpp"
 
@@ -2299,89 +2301,107 @@ __global__ void __launch_bounds__(kBlock) k_lattice(KArgs A, int part) {
 // matrix of weights, A[m][k] = W(k - 8 - m, ny, nz), times the 32 inputs
 // around them; 16 node rows (y) make the columns: one 16x16x32 MFMA per row
 // and plane, and half a second one (the wing) for rows with more than 8 taps
-// to a side.  Weights and inputs are split into two float16 numbers each (x s =
-// hi + lo with s a power of two, 22 bits; the inputs' s from the largest |q| of
-// the staged window, so nothing overflows and values down to 2^-38 of it
-// count), and the products hi hi + hi lo + lo hi are exact in float32; the sums
-// are flushed to float64 after every pair of rows +-ny of 4 planes.
+// to a side.  The inputs of the rows +ny and -ny are added first.
+//
+// Weights and inputs are float32 numbers in three bfloat16 parts each, which
+// hold them exactly at every magnitude.  Six of the nine products are formed;
+// the other three are below 2^-24 of the whole.  The leading product and the
+// sum of the others have accumulators of their own, flushed to float64 after
+// every row pair of 4 planes.  Against float64, root mean square over the nodes
+// of a level, relative: 5.1e-7, 3.4e-7 and 3.1e-7 for 24,000 atoms in water
+// (cubic, a = 12, h = 2), 3.9e-7 and 3.2e-7 for 9,000 periodic (quintic, a = 10),
+// 6.8e-8 for 1,000 charges; chains of float32 FMAs have 1.07e-6, 6.5e-7 and
+// 4.9e-7, 8.5e-7 and 6.8e-7, 7.0e-8.  (Two float16 parts and three products, 23
+// instead of 31 us at 24,000 atoms, have 1.16e-6, 8.4e-7 and 6.5e-7, 8.5e-7 and
+// 6.7e-7, 1.5e-7, and lose what is below 2^-38 of a window's largest input.)
 //
 // A block owns 16 x 16 x ZB nodes.  A phase takes 4 planes nz: its input planes
-// are staged once (split into the two halves on the way, zero outside the
-// grid), and every staged fragment of a row (16 bytes per lane and half) serves
-// the 4 planes it is an input of, so the matrix pipe, not LDS, is the limit:
-// 12 MFMAs per 2 LDS reads.  The 4 waves split the phase's rows.  The weights'
-// fragments come from the L2 (the same for every block); +ny and -ny share them.
+// are staged once (zero outside the grid), and every fragment read of a row pair
+// (8 values per lane and row, split in registers) serves the 4 planes it is an
+// input of.  The 4 waves split the phase's row pairs.  The weights' fragments
+// come from the L2 (the same for every block).  Bound by the matrix pipe and by
+// staging: with one product of the six, 19 us instead of 31 at 24,000 atoms and
+// 70 instead of 112 at 1M; without the splits 29 and 112.
 // --------------------------------------------------------------------------
-typedef _Float16 half8 __attribute__((ext_vector_type(8)));
-typedef _Float16 half2v __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float floatx2 __attribute__((ext_vector_type(2)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 struct __attribute__((packed, aligned(4))) float4_a4 {
   float v[4];
 };
 
-// acc[z] += the 4 planes' fragments (weights ah, al) against the staged input
-// planes [zlo, zhi) (hi, lo; `plane` values apart) of one row of ZB output
-// planes: input plane zi is plane j's input of output zi - j.
-template <int ZB>
-__device__ __forceinline__ void lat_row(floatx4* acc, const half8* ah, const half8* al, const _Float16* hi,
-                                        const _Float16* lo, int plane, int zlo, int zhi) {
-  half8 nh = *reinterpret_cast<const half8*>(hi), nl = *reinterpret_cast<const half8*>(lo);
+// Three bfloat16 parts of 8 weights or inputs per lane, largest first: each the
+// nearest to what the ones before it leave, so they add up to a float exactly.
+struct Split8 {
+  bf16x8 p[3];
+};
+
+// 8 inputs of the rows at `up` and `down`.
+struct RowPair {
+  float4 up[2], down[2];
+};
+__device__ __forceinline__ RowPair lat_read(const float* up, const float* down) {
+  RowPair r;
 #pragma unroll
-  for (int zi = 0; zi < ZB + kLatPlanes - 1; ++zi) {
-    // the next plane's fragments are read while this plane's products run
-    // (the barrier keeps the scheduler from reading every plane at once)
-    const half8 bh = nh, bl = nl;
-    if (zi + 1 < ZB + kLatPlanes - 1) {
-      nh = *reinterpret_cast<const half8*>(hi + (zi + 1) * plane);
-      nl = *reinterpret_cast<const half8*>(lo + (zi + 1) * plane);
-    }
-    if (zi >= zlo && zi < zhi) {                       // (planes outside the grid are zero)
-      // product by product over the planes: dependent MFMAs stay apart
-#pragma unroll
-      for (int j = 0; j < kLatPlanes; ++j)
-        if (zi - j >= 0 && zi - j < ZB)
-          acc[zi - j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(al[j], bh, acc[zi - j], 0, 0, 0);
-#pragma unroll
-      for (int j = 0; j < kLatPlanes; ++j)
-        if (zi - j >= 0 && zi - j < ZB)
-          acc[zi - j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[j], bl, acc[zi - j], 0, 0, 0);
-#pragma unroll
-      for (int j = 0; j < kLatPlanes; ++j)
-        if (zi - j >= 0 && zi - j < ZB)
-          acc[zi - j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(ah[j], bh, acc[zi - j], 0, 0, 0);
-    }
-    __builtin_amdgcn_sched_barrier(0);
+  for (int i = 0; i < 2; ++i) {
+    r.up[i] = reinterpret_cast<const float4*>(up)[i];
+    r.down[i] = reinterpret_cast<const float4*>(down)[i];
   }
+  return r;
 }
 
-// The same for the wings: the lower half-wave reads input plane zi, the upper
-// one plane zi + 1, so one fragment pair serves stencil planes 2p and 2p + 1.
-template <int ZB>
-__device__ __forceinline__ void lat_wing(floatx4* acc, const half8* wh, const half8* wl, const _Float16* hi,
-                                         const _Float16* lo, int plane, int zlo, int zhi) {
-  half8 nh = *reinterpret_cast<const half8*>(hi), nl = *reinterpret_cast<const half8*>(lo);
+__device__ __forceinline__ Split8 lat_split(const RowPair& r) {
+  Split8 s;
+  auto two = [&](int at, float x0, float x1) {
+    floatx2 x = {x0, x1};
 #pragma unroll
-  for (int zi = 0; zi < ZB + 2; ++zi) {
-    const half8 bh = nh, bl = nl;
-    if (zi + 1 < ZB + 2) {
-      nh = *reinterpret_cast<const half8*>(hi + (zi + 1) * plane);
-      nl = *reinterpret_cast<const half8*>(lo + (zi + 1) * plane);
+    for (int i = 0; i < 3; ++i) {
+      const bf16x2 near = __builtin_convertvector(x, bf16x2);
+      if (i < 2) x = x - __builtin_convertvector(near, floatx2);
+      s.p[i][at] = near[0];
+      s.p[i][at + 1] = near[1];
     }
-    if (zi + 1 >= zlo && zi < zhi) {
+  };
 #pragma unroll
-      for (int p = 0; p < 2; ++p)
-        if (zi - 2 * p >= 0 && zi - 2 * p < ZB)
-          acc[zi - 2 * p] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wl[p], bh, acc[zi - 2 * p], 0, 0, 0);
+  for (int i = 0; i < 2; ++i) {
+    two(4 * i, r.up[i].x + r.down[i].x, r.up[i].y + r.down[i].y);
+    two(4 * i + 2, r.up[i].z + r.down[i].z, r.up[i].w + r.down[i].w);
+  }
+  return s;
+}
+
+// The sums of the leading products and those of the others.
+struct LatAcc {
+  floatx4 lead, rest;
+};
+
+// acc[z] += the fragments a[j], j = 0 .. J - 1, against the staged input planes
+// [zlo, zhi) (`plane` values apart) of a row pair of ZB output planes: input
+// plane zi is fragment j's input of output zi - STEP j.
+template <int ZB, int J, int STEP, int NZ>
+__device__ __forceinline__ void lat_products(LatAcc* acc, const Split8* a, const float* up, const float* down,
+                                             int plane, int zlo, int zhi) {
+  Split8 b = lat_split(lat_read(up, down));
 #pragma unroll
-      for (int p = 0; p < 2; ++p)
-        if (zi - 2 * p >= 0 && zi - 2 * p < ZB)
-          acc[zi - 2 * p] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wh[p], bl, acc[zi - 2 * p], 0, 0, 0);
+  for (int zi = 0; zi < NZ; ++zi) {
+    // the next plane's inputs are read while this plane's products run (the
+    // barrier keeps the scheduler from reading every plane at once)
+    RowPair next;
+    if (zi + 1 < NZ) next = lat_read(up + (zi + 1) * plane, down + (zi + 1) * plane);
+    if (zi >= zlo && zi < zhi) {                       // (planes outside the grid are zero)
+      // product by product over the planes: dependent MFMAs stay apart
+      constexpr int pa[6] = {1, 2, 0, 1, 0, 0}, pb[6] = {1, 0, 2, 0, 1, 0};
 #pragma unroll
-      for (int p = 0; p < 2; ++p)
-        if (zi - 2 * p >= 0 && zi - 2 * p < ZB)
-          acc[zi - 2 * p] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wh[p], bh, acc[zi - 2 * p], 0, 0, 0);
+      for (int t = 0; t < 6; ++t)
+#pragma unroll
+        for (int j = 0; j < J; ++j)
+          if (zi - STEP * j >= 0 && zi - STEP * j < ZB) {
+            floatx4& c = t == 5 ? acc[zi - STEP * j].lead : acc[zi - STEP * j].rest;
+            c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[j].p[pa[t]], b.p[pb[t]], c, 0, 0, 0);
+          }
     }
+    if (zi + 1 < NZ) b = lat_split(next);
     __builtin_amdgcn_sched_barrier(0);
   }
 }
@@ -2394,7 +2414,6 @@ __global__ void __launch_bounds__(ZS * 4 * kWave, 2) k_lattice_mfma(KArgs A, int
   constexpr int kLatWaves = 4 * ZS;
   int blk;
   __shared__ __align__(16) SysDesc sdesc;
-  __shared__ int wmax[kLatWaves];
   const SysDesc& S = stage_desc(sys_of(A, blk, false), &sdesc);
   const Geom& g = S.g;
   const LatLaunch& P = S.lat;
@@ -2436,8 +2455,7 @@ __global__ void __launch_bounds__(ZS * 4 * kWave, 2) k_lattice_mfma(KArgs A, int
   const int plane = rows * pitch;
   constexpr int NP = ZB * ZS + kLatPlanes - 1;          // input planes of a phase
   extern __shared__ float4 lds4[];
-  _Float16* hi = reinterpret_cast<_Float16*>(lds4);
-  _Float16* lo = hi + NP * plane;
+  float* win = reinterpret_cast<float*>(lds4);
   // staging: a thread takes one octet (8 x values) of one row, in planes sp .. sp + NPT - 1
   constexpr int NPT = (NP + ZS - 1) / ZS;               // planes per thread
   const int st = (int)threadIdx.x & 255, sp = NPT * uniform((int)threadIdx.x >> 8);
@@ -2463,9 +2481,11 @@ __global__ void __launch_bounds__(ZS * 4 * kWave, 2) k_lattice_mfma(KArgs A, int
     for (int r = 0; r < 4; ++r) tot[z][r] = 0.0;
   const uint4* __restrict__ frags = reinterpret_cast<const uint4*>((const void*)S.d.lat_frags) + lane;
   constexpr int kFrag = kLatFragBytes / 16;
-  auto fragment = [&](int id, half8& fh, half8& fl) {
-    fh = __builtin_bit_cast(half8, frags[id * kFrag]);
-    fl = __builtin_bit_cast(half8, frags[id * kFrag + kWave]);
+  auto fragment = [&](int id) {
+    Split8 f;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) f.p[i] = __builtin_bit_cast(bf16x8, frags[id * kFrag + i * kWave]);
+    return f;
   };
   const int ph0 = phases * grp / G, ph1 = phases * (grp + 1) / G;
   float4_a4 v[NPT][2];
@@ -2491,17 +2511,15 @@ __global__ void __launch_bounds__(ZS * 4 * kWave, 2) k_lattice_mfma(KArgs A, int
       continue;
     }
     const int zlo = max(0, -(zw + nz0)), zhi = NZ - (zw + nz0);   // the wave's input planes that do
-    // the wave's rows of the phase: row i stands for ny = 0 (i = 0), +(i + 1)/2
-    // (odd i) or -(i + 1)/2; the plan cuts them into shares of equal cost
-    const int i1 = uniform(P.cut[ph][wk + 1]);
-    int i = uniform(P.cut[ph][wk]);
-    // fragments of the wave's first row, on their way while the window is staged
-    half8 ah[kLatPlanes], al[kLatPlanes];
+    // the wave's row pairs ny = +-ay; the plan cuts them into shares of equal cost
+    const int ay0 = uniform(P.cut[ph][wk]), ay1 = uniform(P.cut[ph][wk + 1]);
+    // fragments of the wave's first pair, on their way while the window is staged
+    Split8 a[kLatPlanes];
     auto main_fragments = [&](int ay) {
 #pragma unroll
-      for (int j = 0; j < kLatPlanes; ++j) fragment(abs(nz0 + j) * H1 + ay, ah[j], al[j]);
+      for (int j = 0; j < kLatPlanes; ++j) a[j] = fragment(abs(nz0 + j) * H1 + ay);
     };
-    main_fragments((i + 1) >> 1);
+    main_fragments(ay0);
     if (__any(sok && skeep < 8)) {
 #pragma unroll
       for (int p = 0; p < NPT; ++p)
@@ -2509,74 +2527,40 @@ __global__ void __launch_bounds__(ZS * 4 * kWave, 2) k_lattice_mfma(KArgs A, int
         for (int e = 0; e < 8; ++e)
           if (e >= skeep) v[p][e >> 2].v[e & 3] = 0.f;
     }
-    // inputs are taken times a power of two: the largest |q| of the window lands in [2^13, 2^14)
-    float vm = 0.f;
-#pragma unroll
-    for (int p = 0; p < NPT; ++p)
-#pragma unroll
-      for (int e = 0; e < 8; e += 2)
-        vm = fmaxf(vm, fmaxf(fabsf(v[p][e >> 2].v[e & 3]), fabsf(v[p][e >> 2].v[(e & 3) + 1])));
-    const int wm = wave_max_s(__float_as_int(vm));
-    __syncthreads();                                    // the previous phase is done with the window (and wmax)
-    if (lane == 0) wmax[wave] = wm;
-    __syncthreads();
-    int qbits = wmax[0];
-#pragma unroll
-    for (int w = 1; w < kLatWaves; ++w) qbits = max(qbits, wmax[w]);
-    const int sbits = min(254, max(1, 267 - ((uniform(qbits) >> 23) & 255)));
-    const float qscale = __int_as_float(sbits << 23);
+    __syncthreads();                                    // the previous phase is done with the window
     if (smine) {
 #pragma unroll
       for (int p = 0; p < NPT; ++p) {
         if (sp + p >= NP) break;
-        half8 h, l;
-#pragma unroll
-        for (int e = 0; e < 8; e += 2) {
-          floatx2 x = {v[p][e >> 2].v[e & 3] * qscale, v[p][e >> 2].v[(e & 3) + 1] * qscale};
-          const half2v hh = __builtin_convertvector(x, half2v);
-          x = x - __builtin_convertvector(hh, floatx2);
-          const half2v ll = __builtin_convertvector(x, half2v);
-          h[e] = hh[0];
-          h[e + 1] = hh[1];
-          l[e] = ll[0];
-          l[e + 1] = ll[1];
-        }
-        *reinterpret_cast<half8*>(hi + (sp + p) * plane + sdst) = h;
-        *reinterpret_cast<half8*>(lo + (sp + p) * plane + sdst) = l;
+        float4* dst = reinterpret_cast<float4*>(win + (sp + p) * plane + sdst);
+        dst[0] = make_float4(v[p][0].v[0], v[p][0].v[1], v[p][0].v[2], v[p][0].v[3]);
+        dst[1] = make_float4(v[p][1].v[0], v[p][1].v[1], v[p][1].v[2], v[p][1].v[3]);
       }
     }
     if (ph + 1 < ph1) load_planes(ph + 1);              // the next phase's inputs, on their way during this one's products
     __syncthreads();
-    // undoes the scale of the inputs
-    const double unscale = __longlong_as_double((long long)(1023 + 127 - sbits) << 52);
     // the plane of the phase nearest to the centre (the longest rows)
     const int az = nz0 > 0 ? nz0 : max(0, -(nz0 + kLatPlanes - 1));
 #pragma unroll 1
-    while (i < i1) {
-      const int ay = (i + 1) >> 1;
-      // this wave's signs of the row pair, where some of the 16 input rows lie in the grid
-      const bool up = (i == 0 || (i & 1)) && y0 + ay < NY;
-      const bool down = i > 0 && (!(i & 1) || i + 1 < i1) && y0 + 15 - ay >= 0;
-      i += (i & 1) ? 2 : 1;
-      half8 wh[2], wl[2];
+    for (int ay = ay0; ay < ay1; ++ay) {
+      Split8 w[2];
       const bool wing = H > 8 && 81 + ay * ay + az * az <= n2max;
       if (wing)
 #pragma unroll
-        for (int p = 0; p < 2; ++p) fragment((H + kLatPlanes + 2 * ph + p) * H1 + ay, wh[p], wl[p]);
-      floatx4 acc[ZB];
+        for (int p = 0; p < 2; ++p) w[p] = fragment((H + kLatPlanes + 2 * ph + p) * H1 + ay);
+      LatAcc acc[ZB];
 #pragma unroll
-      for (int z = 0; z < ZB; ++z) acc[z] = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 1
-      for (int sgn = up ? 1 : -1; sgn >= (down ? -1 : 1); sgn -= 2) {
-        const int d = sgn * ay * pitch;
-        lat_row<ZB>(acc, ah, al, hi + main_at + d, lo + main_at + d, plane, zlo, zhi);
-        if (wing) lat_wing<ZB>(acc, wh, wl, hi + wing_at + d, lo + wing_at + d, plane, zlo, zhi);
-      }
-      if (i < i1) main_fragments((i + 1) >> 1);         // the next row's, on their way during the sums
+      for (int z = 0; z < ZB; ++z) acc[z].lead = acc[z].rest = floatx4{0.f, 0.f, 0.f, 0.f};
+      const int d = ay * pitch;
+      lat_products<ZB, kLatPlanes, 1, ZB + kLatPlanes - 1>(acc, a, win + main_at + d, win + main_at - d, plane, zlo, zhi);
+      // the wings: the lower half-wave reads input plane zi, the upper one
+      // plane zi + 1, so one fragment serves stencil planes 2p and 2p + 1
+      if (wing) lat_products<ZB, 2, 2, ZB + 2>(acc, w, win + wing_at + d, win + wing_at - d, plane, zlo - 1, zhi);
+      if (ay + 1 < ay1) main_fragments(ay + 1);          // on their way during the sums
 #pragma unroll
       for (int z = 0; z < ZB; ++z)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) tot[z][r] = fma((double)acc[z][r], unscale, tot[z][r]);
+        for (int r = 0; r < 4; ++r) tot[z][r] += (double)acc[z].lead[r] + (double)acc[z].rest[r];
     }
   }
   // the waves' totals meet in LDS and are added in wave order, each wave taking
@@ -2588,9 +2572,8 @@ __global__ void __launch_bounds__(ZS * 4 * kWave, 2) k_lattice_mfma(KArgs A, int
 #pragma unroll
     for (int r = 0; r < 4; ++r) red[((wave * ZB + z) * 4 + r) * kWave + lane] = tot[z][r];
   __syncthreads();
-  // undo the scale of the weights; a tile in one block also the level's 2^-k
-  // (the consumers of partials apply it to their sum)
-  const double wscale = __longlong_as_double((long long)(1023 - uniform(P.wexp) - (G == 1 ? level : 0)) << 52);
+  // a tile in one block applies the level's 2^-k (else the consumers of the partials)
+  const double wscale = __longlong_as_double((long long)(1023 - (G == 1 ? level : 0)) << 52);
   float* __restrict__ ucut = S.d.ucut + lv_off;
   double* __restrict__ out = S.d.lat_part + uniform(P.t[li].part0) + (size_t)grp * uniform(g.lv[level].count);
   const int y = y0 + col;
@@ -3649,7 +3632,7 @@ hipError_t launch_eval(int mode, const LaunchGeom& L, hipStream_t s, const Io& i
     if (L.lat_b == 4) {
       MSM_LAT(4, 1);
     } else if (L.lat_b == 6) {
-      MSM_LAT(6, 1);
+      MSM_LAT(3, 2);
     } else if (L.lat_b == 8) {
       MSM_LAT(4, 2);
     } else {
