@@ -1272,20 +1272,30 @@ static msm_status check_call(const msm_plan* P, const void* ws, size_t ws_bytes,
   return MSM_OK;
 }
 
-msm_status msm_compute(const msm_plan* P, void* ws, size_t ws_bytes, msm_stream_t stream,
-                       const float* x, const float* y, const float* z, const float* q, float* fx,
-                       float* fy, float* fz, float* phi, double* energy, double* virial) {
-  msm_status st = check_call(P, ws, ws_bytes, x, y, z, q, fx, fy, fz);
+}  // extern "C"
+
+msm_status plan_eval(const msm_plan* P, void* ws, size_t ws_bytes, msm_stream_t stream, const msm::Io& io,
+                     bool potential) {
+  msm_status st = check_call(P, ws, ws_bytes, io.x, io.y, io.z, io.q, io.fx, io.fy, io.fz);
   if (st != MSM_OK) return st;
   msm_plan* M = const_cast<msm_plan*>(P);
   hipError_t e = ensure_aux(M->aux);
   if (e != hipSuccess) return hip_fail(e, "create auxiliary stream");
-  const msm::Io io{x, y, z, q, fx, fy, fz, phi, energy, virial, nullptr};
-  e = msm::launch_eval(msm::kModeForces, launch_geom(P, ws), reinterpret_cast<hipStream_t>(stream), io,
+  msm::LaunchGeom L = launch_geom(P, ws);
+  L.potential = potential;
+  e = msm::launch_eval(msm::kModeForces, L, reinterpret_cast<hipStream_t>(stream), io,
                        P->profile ? M->ev : nullptr, &M->aux.cc, P->profile == 2);
   if (P->profile) M->profiled = true;
   if (e != hipSuccess) return hip_fail(e, "kernel launch");
   return MSM_OK;
+}
+
+extern "C" {
+
+msm_status msm_compute(const msm_plan* P, void* ws, size_t ws_bytes, msm_stream_t stream,
+                       const float* x, const float* y, const float* z, const float* q, float* fx,
+                       float* fy, float* fz, float* phi, double* energy, double* virial) {
+  return plan_eval(P, ws, ws_bytes, stream, msm::Io{x, y, z, q, fx, fy, fz, phi, energy, virial, nullptr}, false);
 }
 
 static msm_status eval_mode(int mode, const msm_plan* P, void* ws, size_t ws_bytes,

@@ -367,7 +367,7 @@ msm_status msm_batch_workspace_init(const msm_batch* Bt, void* ws, size_t ws_byt
 }
 
 static msm_status batch_eval(int mode, const msm_batch* Bt, void* ws, size_t ws_bytes,
-                             msm_stream_t stream, const msm::Io& io, msm_graph** graph) {
+                             msm_stream_t stream, const msm::Io& io, msm_graph** graph, bool potential = false) {
   msm_status st = check_batch(Bt, ws, ws_bytes);
   if (st != MSM_OK) return st;
   if (Bt->total_atoms > 0 && (!io.x || !io.y || !io.z || !io.q))
@@ -378,6 +378,7 @@ static msm_status batch_eval(int mode, const msm_batch* Bt, void* ws, size_t ws_
   hipError_t e = ensure_aux(M->aux);
   if (e != hipSuccess) return hip_fail(e, "create auxiliary stream");
   msm::LaunchGeom L = Bt->lg;
+  L.potential = potential;
   point_into(M, ws, L);
   if (graph) {
     L.streams = L.capture_streams;
@@ -585,15 +586,9 @@ static msm_status autotune(bool batch, void* obj, void* ws, size_t ws_bytes, msm
   hipEvent_t e0 = nullptr, e1 = nullptr;
   hipError_t he = hipEventCreate(&e0);
   if (he == hipSuccess) he = hipEventCreate(&e1);
-  // the timed evaluations return an energy: without one (and potentials) they
-  // would run the short range that sums forces alone
-  double* energy = nullptr;
-  if (he == hipSuccess)
-    he = hipMalloc((void**)&energy, sizeof(double) * (size_t)(batch ? static_cast<msm_batch*>(obj)->n_sys : 1));
   if (he != hipSuccess) {
     if (e0) (void)hipEventDestroy(e0);
-    if (e1) (void)hipEventDestroy(e1);
-    return hip_fail(he, "create timing events and energy output");
+    return hip_fail(he, "create timing events");
   }
   msm_batch* Bt = batch ? static_cast<msm_batch*>(obj) : nullptr;
   msm_plan* P = batch ? nullptr : static_cast<msm_plan*>(obj);
@@ -601,11 +596,13 @@ static msm_status autotune(bool batch, void* obj, void* ws, size_t ws_bytes, msm
   auto tune = [&](const msm_tuning& t) {
     return batch ? msm_batch_tune(Bt, ws, ws_bytes, stream, &t) : msm_plan_tune(P, ws, ws_bytes, stream, &t);
   };
+  // the timed evaluations have no output (the library owns no device memory for
+  // one), but sum potentials: otherwise they would run the short range that
+  // sums forces alone
+  const msm::Io io{x, y, z, q, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
   auto eval = [&]() {
-    return batch ? msm_batch_compute(Bt, ws, ws_bytes, stream, x, y, z, q, nullptr, nullptr, nullptr, nullptr,
-                                     energy, nullptr)
-                 : msm_compute(P, ws, ws_bytes, stream, x, y, z, q, nullptr, nullptr, nullptr, nullptr,
-                               energy, nullptr);
+    return batch ? batch_eval(msm::kModeForces, Bt, ws, ws_bytes, stream, io, nullptr, true)
+                 : plan_eval(P, ws, ws_bytes, stream, io, true);
   };
   auto describe = [](const msm_tuning& t) {
     return "\"lattice_b\": " + std::to_string(t.lattice_b) + ", \"item_chunks\": " + std::to_string(t.item_chunks) +
@@ -716,7 +713,6 @@ static msm_status autotune(bool batch, void* obj, void* ws, size_t ws_bytes, msm
   }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
-  (void)hipFree(energy);
   if (st != MSM_OK) return st;
   st = tune(bt);
   if (st != MSM_OK) return st;

@@ -340,6 +340,7 @@ struct LaunchGeom {
                                      // 3: the coarse lattice cutoff
   int short_split = 1000;            // per mille of its work items started there (the rest after the
                                      // lattice cutoff)
+  bool potential = false;            // sum potentials although no output reads them (the autotuner's evaluations)
   int short_parts = 1;               // row parts side by side: short-range blocks of 4 short_parts waves
   bool short_split_rows = false;     // some system sums its rows in parts
   StageGrid zero, atoms, one, shortr, anterp, top, energy;

@@ -3525,7 +3525,7 @@ hipError_t launch_eval(int mode, const LaunchGeom& L, hipStream_t s, const Io& i
     // potentials nor an energy (the steps of a trajectory, an energy gradient
     // without dE/dq): those pairs sum forces alone (three velocity Verlet
     // steps of 50,000 atoms: 636 us; 664 with the potential).
-    const bool pot = mode == kModeEnergy || io.phi != nullptr || io.energy != nullptr;
+    const bool pot = mode == kModeEnergy || io.phi != nullptr || io.energy != nullptr || L.potential;
 #define MSM_SHORT_S(MM, FF, PP, KK, PE)                                                                      \
   do {                                                                                                       \
     if (L.short_split_rows) {                                                                                \

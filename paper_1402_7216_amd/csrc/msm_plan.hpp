@@ -91,6 +91,10 @@ void set_anterp_tiles(Geom& g, int target);
 // captured graphs (short_parts and blocks are those of the whole launch).
 void default_streams(msm::LaunchGeom& L, bool periodic);
 
+// msm_compute on io's buffers; potential: sum potentials even if no output reads them.
+msm_status plan_eval(const msm_plan* P, void* ws, size_t ws_bytes, msm_stream_t stream, const msm::Io& io,
+                     bool potential);
+
 // Number of systems and total atom count of a batch (the concatenated arrays'
 // length).
 msm_status batch_shape(const msm_batch* B, int32_t* n_sys, int32_t* total_atoms);
