@@ -170,12 +170,13 @@ msm_status msm_compute(const msm_plan* plan, void* ws, size_t ws_bytes, msm_stre
  * for callers that cannot allocate device memory (code under stream capture,
  * tight serving loops, harnesses that forbid allocation).  Same arguments and
  * results as msm_compute minus ws/ws_bytes; every stage runs in order on
- * `stream`.  The workspace is a 65 MiB array (64 MiB and a plan's lattice
+ * `stream`.  The workspace is a 66 MiB array (64 MiB and a plan's lattice
  * weight fragments) in the library's device data, one copy per GPU, held until
  * the process ends; plans whose workspace (msm_workspace_bytes) exceeds it are
- * rejected with MSM_ERR_UNSUPPORTED before anything runs.  The array keeps the last call's contents: the first
- * call of a plan on a device (and the first after a re-tune, or after another
- * plan's call) uploads the plan's tables into it and synchronises `stream`.
+ * rejected with MSM_ERR_UNSUPPORTED before anything runs.  The array keeps the
+ * last call's contents: the first call of a plan on a device (and the first
+ * after a re-tune, or after another plan's call) uploads the plan's tables into
+ * it and synchronises `stream`.
  * All calls on one GPU share the array, so calls that overlap on one GPU (two
  * streams, two threads) race and give undefined results.  Data errors (non-
  * finite input, atoms outside the box, coincident atoms) are not reported on

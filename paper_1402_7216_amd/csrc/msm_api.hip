@@ -319,6 +319,16 @@ void choose_lattice_tiles(const Geom& g, int H_, msm::LatLaunch& lat, int force_
   }
 }
 
+// The plan's tiles, and the largest need of partials of any tuning.
+void set_lattice_tiles(msm_plan* P, int H) {
+  P->lat_part_max = 0;
+  for (int b : {4, 6, 8}) {
+    choose_lattice_tiles(P->g, H, P->lat, b);
+    P->lat_part_max = std::max(P->lat_part_max, P->lat.n_part);
+  }
+  choose_lattice_tiles(P->g, H, P->lat);
+}
+
 // Least squares min |A c - b| over the columns of A (rows x cols, row-major)
 // by Householder reflections; A and b are overwritten.
 void householder_lsq(std::vector<double>& A, std::vector<double>& b, int rows, int cols, double* c) {
@@ -959,12 +969,7 @@ msm_status msm_plan_create(const msm_params* prm, int32_t n_atoms, msm_plan** ou
         return gamma_h(c, g.m, dist / a) / a - gamma_h(c, g.m, dist / (2.0 * a)) / (2.0 * a);
       };
       lattice_fragments(H, 2.0 * a / h, weight, P->lat, P->lat_frags);
-      // the partials section holds the largest need of any tuning
-      for (int b : {4, 6, 8}) {
-        choose_lattice_tiles(g, H, P->lat, b);
-        P->lat_part_max = std::max(P->lat_part_max, P->lat.n_part);
-      }
-      choose_lattice_tiles(g, H, P->lat);
+      set_lattice_tiles(P, H);
     } else {
       P->lat.b = 0;
       P->lat.H = H;
@@ -1009,22 +1014,33 @@ msm_status msm_plan_create(const msm_params* prm, int32_t n_atoms, msm_plan** ou
   lay.bytes[msm::kSecBinHist] = std::max<size_t>((size_t)P->max_bin_hist, 1) * sizeof(int);
   // tile totals of the four-kernel binning's scan, or the row starts of the row binning
   lay.bytes[msm::kSecScan] = ((size_t)P->max_cells + 1) * sizeof(int);
-  // the anterpolation's partials and, once q^0 is gathered from them, the
-  // lattice cutoff's share one section
-  lay.bytes[msm::kSecAntPart] = std::max((size_t)g.atn[0] * g.atn[1] * g.atn[2] * g.at_ext * sizeof(long long),
-                                         P->lat_part_max * sizeof(double));
   lay.bytes[msm::kSecRows] = std::max<size_t>(P->rows.size(), 1) * sizeof(msm::StencilRow);
   lay.bytes[msm::kSecWeights] = std::max<size_t>(P->weights.size(), 1) * sizeof(float);
   lay.bytes[msm::kSecLatFrags] = std::max<size_t>(P->lat_frags.size(), 1) * sizeof(uint16_t);
   lay.bytes[msm::kSecTop] = P->top.size() * sizeof(double);
   lay.bytes[msm::kSecPartials] = 10 * (size_t)P->n_partials * sizeof(double);
   lay.bytes[msm::kSecDesc] = sizeof(msm::SysDesc);
-  size_t o = 0;
-  for (int s = 0; s < msm::kSecCount; ++s) {
-    lay.off[s] = o;
-    o += align256(lay.bytes[s]);
+  // the anterpolation's partials and, once q^0 is gathered from them, the
+  // lattice cutoff's share one section
+  const size_t ant_bytes = (size_t)g.atn[0] * g.atn[1] * g.atn[2] * g.at_ext * sizeof(long long);
+  auto place = [&]() {
+    lay.bytes[msm::kSecAntPart] = std::max(ant_bytes, P->lat_part_max * sizeof(double));
+    size_t o = 0;
+    for (int s = 0; s < msm::kSecCount; ++s) {
+      lay.off[s] = o;
+      o += align256(lay.bytes[s]);
+    }
+    lay.total = o;
+  };
+  place();
+  // a plan that the lattice's partials alone keep out of msm_compute_static
+  // (many atoms on a small grid) splits its tiles less
+  if (lay.total > msm::kStaticBytes && P->lat.b > 0 &&
+      lay.total - align256(lay.bytes[msm::kSecAntPart]) + align256(ant_bytes) <= msm::kStaticBytes) {
+    g.part_cap = (long long)(ant_bytes / sizeof(double));
+    set_lattice_tiles(P, P->lat.H);
+    place();
   }
-  lay.total = o;
 
   refresh_launch(P);
   *out = P;

@@ -12,6 +12,8 @@
 namespace msm {
 
 constexpr int kMaxLevels = 12;
+constexpr size_t kStaticBytes = size_t(66) << 20;   // workspace of msm_compute_static: 64 MiB and a plan's lattice
+                                                    // weight fragments (1.3 MiB at most)
 constexpr int kShortWaves = 4;           // waves of a short-range block (they split the neighbour rows)
 constexpr int kShortParts = 4;           // parts a small system sums a wave's rows in, side by side in blocks of 16 waves
 constexpr int kShortSmallItems = 256;    // short-range work items up to which a system is small (one block per CU)

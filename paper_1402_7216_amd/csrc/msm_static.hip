@@ -11,7 +11,7 @@
 
 namespace {
 
-constexpr size_t kScratchBytes = size_t(65) << 20;   // 64 MiB and a plan's lattice weight fragments (under 1 MiB)
+constexpr size_t kScratchBytes = msm::kStaticBytes;
 constexpr int kMaxDevices = 64;
 
 // The workspace of msm_compute_static.  In host code this name stands for the
