@@ -60,7 +60,8 @@ void destroy_aux(AuxStreams& A) {
     if (ss->fork) (void)hipEventDestroy(ss->fork);
     if (ss->join) (void)hipEventDestroy(ss->join);
   }
-  A = AuxStreams{};
+  A.cc = msm::Concurrency{};
+  A.device = -1;
 }
 
 namespace {
@@ -1295,6 +1296,7 @@ msm_status plan_eval(const msm_plan* P, void* ws, size_t ws_bytes, msm_stream_t 
   msm_status st = check_call(P, ws, ws_bytes, io.x, io.y, io.z, io.q, io.fx, io.fy, io.fz);
   if (st != MSM_OK) return st;
   msm_plan* M = const_cast<msm_plan*>(P);
+  std::lock_guard<std::mutex> lock(M->aux.mu);
   hipError_t e = ensure_aux(M->aux);
   if (e != hipSuccess) return hip_fail(e, "create auxiliary stream");
   msm::LaunchGeom L = launch_geom(P, ws);
@@ -1321,6 +1323,7 @@ static msm_status eval_mode(int mode, const msm_plan* P, void* ws, size_t ws_byt
   msm_status st = check_call(P, ws, ws_bytes, x, y, z, q, fx, fy, fz);
   if (st != MSM_OK) return st;
   msm_plan* M = const_cast<msm_plan*>(P);
+  std::lock_guard<std::mutex> lock(M->aux.mu);
   hipError_t e = ensure_aux(M->aux);
   if (e != hipSuccess) return hip_fail(e, "create auxiliary stream");
   const msm::Io io{x, y, z, q, fx, fy, fz, phi, energy, nullptr, gscale};
@@ -1366,6 +1369,7 @@ msm_status msm_graph_capture(const msm_plan* P, void* ws, size_t ws_bytes, const
   msm_status st = check_call(P, ws, ws_bytes, x, y, z, q, fx, fy, fz);
   if (st != MSM_OK) return st;
   msm_plan* M = const_cast<msm_plan*>(P);
+  std::lock_guard<std::mutex> lock(M->aux.mu);
   hipError_t e = ensure_aux(M->aux);
   if (e != hipSuccess) return hip_fail(e, "create auxiliary stream");
   const msm::Io io{x, y, z, q, fx, fy, fz, phi, energy, virial, nullptr};

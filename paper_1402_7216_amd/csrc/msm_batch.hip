@@ -375,6 +375,7 @@ static msm_status batch_eval(int mode, const msm_batch* Bt, void* ws, size_t ws_
   if (!((io.fx && io.fy && io.fz) || (!io.fx && !io.fy && !io.fz)))
     return fail(MSM_ERR_INVALID_ARG, "vector outputs must be all set or all null");
   msm_batch* M = const_cast<msm_batch*>(Bt);
+  std::lock_guard<std::mutex> lock(M->aux.mu);
   hipError_t e = ensure_aux(M->aux);
   if (e != hipSuccess) return hip_fail(e, "create auxiliary stream");
   msm::LaunchGeom L = Bt->lg;

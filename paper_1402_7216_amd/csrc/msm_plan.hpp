@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <mutex>
 #include <set>
 #include <string>
 #include <vector>
@@ -17,6 +18,8 @@ using msm::Layout;
 struct AuxStreams {
   msm::Concurrency cc;
   int device = -1;
+  std::mutex mu;           // held while an evaluation is enqueued: its fork event must not be recorded again by
+                           // another thread's call on the same plan before the side stream waits for it
 };
 
 struct msm_plan {
@@ -24,7 +27,7 @@ struct msm_plan {
   msm_pair_params pp{};                      // parameters of a pair-method plan (g.pair != 0)
   Geom g;
   std::vector<msm::StencilRow> rows;         // full stencil rows (untiled lattice kernel)
-  std::vector<uint16_t> lat_frags;           // weight fragments of the tiled lattice kernel (float16 bits)
+  std::vector<uint16_t> lat_frags;           // weight fragments of the tiled lattice kernel (bfloat16 bits)
   std::vector<float> weights;                // full stencil weights
   std::vector<double> top;                   // FP64 top-level kernel table
   int n_partials = 1;
