@@ -206,64 +206,70 @@ void lattice_fragments(int H, double rad, Weight weight, msm::LatLaunch& lat, st
           octet(n_main + pp * (H + 1) + ay, quad, quad & 1 ? 24 : -16, ay, std::abs(2 * pp + quad / 2 - H));
 }
 
-// Whether row pair +-ay of a phase has taps (1), and wings as well (2).
-int lattice_row(const msm::LatLaunch& lat, int ph, int ay) {
+// Shares a phase's row pairs ny = +-ay among 4 waves with the least largest cost,
+// which it returns (fragment products; a pair with wings counts for one and a
+// half): in contiguous runs, or dealt in turn.  Half-width 9 has four pairs with
+// wings of ten near the centre (3 in runs, 3.5 in turn), 11 eight of twelve (4.5
+// and 4: 31 and 29 us at 24,000 atoms).
+double share_rows(msm::LatLaunch& lat, int ph) {
+  constexpr int waves = 4;
   const int nz0 = msm::kLatPlanes * ph - lat.H;
   const int az = nz0 > 0 ? nz0 : std::max(0, -(nz0 + msm::kLatPlanes - 1));
-  const int n2 = ay * ay + az * az;
-  return n2 > lat.n2max ? 0 : (lat.H > 8 && 81 + n2 <= lat.n2max ? 2 : 1);
-}
-
-// Cuts the row pairs of a phase into contiguous shares of 4 waves with the least
-// largest cost, which it returns (fragment pairs; wings count half).
-double cut_rows(msm::LatLaunch& lat, int ph) {
-  constexpr int waves = 4;
   std::vector<double> cost;
-  for (int ay = 0; ay <= lat.H; ++ay) {
-    const int kind = lattice_row(lat, ph, ay);
-    if (kind == 0) break;
-    cost.push_back(kind == 2 ? 1.5 : 1.0);
+  double turn[waves] = {}, total = 0.0;
+  for (int ay = 0; ay * ay + az * az <= lat.n2max; ++ay) {
+    cost.push_back(lat.H > 8 && 81 + ay * ay + az * az <= lat.n2max ? 1.5 : 1.0);
+    turn[ay % waves] += cost.back();
+    total += cost.back();
   }
-  auto shares = [&](double cap, unsigned char* cut) {
+  const int n = (int)cost.size();
+  unsigned char* share = lat.share[ph];
+  auto runs = [&](double cap) {
     int w = 0;
     double acc = 0.0;
-    cut[0] = 0;
-    for (size_t i = 0; i < cost.size(); ++i) {
-      if (acc + cost[i] > cap + 1e-9) {
+    std::fill(share, share + 2 * waves, (unsigned char)n);
+    share[0] = 0;
+    for (int i = 0; i < n; ++i) {
+      if (acc + cost[i] > cap) {
+        share[waves + w] = (unsigned char)i;
         if (++w == waves) return false;
-        cut[w] = (unsigned char)i;
+        share[w] = (unsigned char)i;
         acc = 0.0;
       }
       acc += cost[i];
     }
-    while (w < waves) cut[++w] = (unsigned char)cost.size();
     return true;
   };
-  double lo = 0.0, hi = 0.0;
-  for (double c : cost) hi += c;
-  unsigned char scratch[sizeof(lat.cut[0])];
-  for (int it = 0; it < 40; ++it) {                        // bisection
-    const double mid = 0.5 * (lo + hi);
-    (shares(mid, scratch) ? hi : lo) = mid;
+  double cap = 0.5 * std::ceil(2.0 * total / waves);           // costs are multiples of one half
+  while (!runs(cap)) cap += 0.5;
+  lat.step[ph] = 1;
+  const double most = *std::max_element(turn, turn + waves);
+  if (most >= cap) return cap;
+  for (int w = 0; w < waves; ++w) {
+    share[w] = (unsigned char)w;
+    share[waves + w] = (unsigned char)n;
   }
-  shares(hi, lat.cut[ph]);
-  return hi;
+  lat.step[ph] = waves;
+  return most;
 }
 
-// Tiles of the lattice-cutoff kernel: planes per block (force_b, or 4: two
-// blocks fit a CU, so one stages its window while the other multiplies), the
-// phases' rows cut into the waves' shares, and the split of each level's phases
-// over blocks: more blocks fill the chip, fewer write and read back fewer
-// partials.  The coarse levels' blocks come last and are split as far as they
-// can be.  Level 0 by an estimate in cycles: a block starts and ends (9,000),
-// each phase stages its window and runs its rows on the matrix pipe, 96 cycles a
-// fragment pair and plane; the work is spread over the blocks that fit the 256
-// compute units, plus the longest block.
-// Stage time with 4, 6 and 8 planes: 1,000 charges 10.6, 12.4, 12.8 us; 9,000
-// periodic 24.2, 24.2, 26.1; 24,000 atoms 31, 35, 36; 1M 113, 145, 132; 1M
-// periodic 58, 75, 66.  Level 0 in 1, 2, 3, 6 blocks a tile: 24,000 atoms 57, 35,
-// 29, 31 us; 100,000 atoms 81, 55, 54, 56 (68 with the coarse levels in 5 and 3
-// blocks); 1M in 1, 2, 3, 5: 112, 129, 119, 124.
+// Tiles of the lattice-cutoff kernel: planes per block (force_b, or 6 where that
+// makes 256 blocks of level 0 and 4 where not; two blocks fit a CU, so one
+// stages its window while the other multiplies), the waves' shares of the
+// phases' rows, and the split of each level's phases over blocks: more blocks
+// fill the chip, fewer write and read back fewer partials.  The coarse levels'
+// blocks come last and are split as far as they can be.  Level 0 by an estimate
+// in cycles: a block starts and ends (9,000), each phase stages its window and
+// runs its rows on the matrix pipe, 96 cycles a fragment and plane.  Blocks that
+// all fit the chip take as long as the longest, sharing its pipes; of more, the
+// work is spread over those that fit, and the longest block ends last.
+// Stage time with 4, 6 and 8 planes: 1,000 charges 10.6, 12.6, 12.8 us; 9,000
+// periodic (96 blocks with 6) 24.4, 28.2, 26.2; 4,096 ions (216) 15.8, 16.6; 24,000
+// atoms (324) 27, 28, 34; 50,000 (315) 31, 28; 100,000 (864) 53, 57, 60; 1M (2880)
+// 112, 109, 132; 1M periodic (1750) 58, 60, 66.  Level 0 in 1, 2, 3, 5, 6 blocks a
+// tile: 24,000 atoms, 4 planes, 53, 32, 27, 28, 30 us; 100,000, 6 planes, 97, 57,
+// 51, 51, 51 (61 with the coarse levels in 5 and 3 blocks); 1M, 6 planes, 1, 2, 3,
+// 5 blocks: 109, 122, 115, 119.
 void choose_lattice_tiles(const Geom& g, int H_, msm::LatLaunch& lat, int force_b = 0) {
   const int phases = lat.phases, n2max = lat.n2max;
   std::memset(&lat, 0, sizeof(lat));
@@ -281,42 +287,64 @@ void choose_lattice_tiles(const Geom& g, int H_, msm::LatLaunch& lat, int force_
     t.ntz = (L.n[2] - 2 * skip + B - 1) / B;
     return (double)t.ntx * t.nty * t.ntz;
   };
-  const int B = force_b ? force_b : 4;
+  msm::LatTile probe{};
+  const int B = force_b ? force_b : (tiles_of(0, 6, probe) * phases < 256.0 ? 4 : 6);
   lat.b = B;
   lat.n = g.levels - 1;
   lat.lds_bytes = msm::lat_lds(H_, B);
   std::vector<double> mat(phases);                         // fragment pairs of each phase's slowest wave
-  for (int ph = 0; ph < phases; ++ph) mat[ph] = cut_rows(lat, ph);
+  for (int ph = 0; ph < phases; ++ph) mat[ph] = share_rows(lat, ph);
   // blocks on the chip at a time (two on a CU share its matrix pipes)
-  const int slots = 256 * (B == 4 && 2 * (lat.lds_bytes + 2048) <= 160 * 1024 ? 2 : 1);
-  int blocks = 0;
-  for (int k = 0; k < g.levels - 1; ++k) {
+  const int slots = 256 * (B < 8 && 2 * (lat.lds_bytes + 2048) <= 160 * 1024 ? 2 : 1);
+  // a block of phases [ph0, ph1): cycles beside the matrix pipe, and on it
+  auto beside = [&](int ph0, int ph1) { return 9000.0 + (3000.0 + 500.0 * (B + 3)) * (ph1 - ph0); };
+  auto matrix = [&](int ph0, int ph1) {
+    double m = 0.0;
+    for (int ph = ph0; ph < ph1; ++ph) m += mat[ph] * 96.0 * msm::kLatPlanes * B * 4 / msm::lat_waves(B);
+    return m;
+  };
+  double coarse = 0.0, coarse_blocks = 0.0;                // cycles and blocks of the coarse levels
+  for (int k = g.levels - 2; k >= 0; --k) {                // (level 0 takes the partials the others leave)
     const msm::Level& L = g.lv[k];
     msm::LatTile t{};
     t.level = k;
+    t.groups = 1;
     const double tiles = tiles_of(k, B, t);
     double best = 1e300;
     for (int G = 1; G <= std::min(msm::kLatMaxGroups, phases); ++G) {
       if (G > 1 && lat.n_part + (double)G * L.count > (double)g.part_cap) break;
-      double sum = 0.0, longest = 0.0;
-      for (int q = 0; q < G; ++q) {
-        double blk = 9000.0;
-        for (int ph = phases * q / G; ph < phases * (q + 1) / G; ++ph)
-          blk += 3000.0 + 500.0 * (B + 3) + mat[ph] * 96.0 * msm::kLatPlanes * B * 4 / msm::lat_waves(B);
-        sum += blk;
-        longest = std::max(longest, blk);
+      if (k > 0) {
+        t.groups = G;
+        continue;
       }
-      const double est = k > 0 ? -G : tiles * sum / slots + longest + (G > 1 ? 0.013 * G * L.count : 0.0);
+      double sum = 0.0, side = 0.0, mm = 0.0;              // all blocks of a tile; its longest block
+      for (int q = 0; q < G; ++q) {
+        const int ph0 = phases * q / G, ph1 = phases * (q + 1) / G;
+        sum += beside(ph0, ph1) + matrix(ph0, ph1);
+        side = std::max(side, beside(ph0, ph1));
+        mm = std::max(mm, matrix(ph0, ph1));
+      }
+      const double total = tiles * G + coarse_blocks;
+      const double est = (total <= slots ? side + 1.05 * mm * std::ceil(total / 256.0) : (tiles * sum + coarse) / slots + side + mm) +
+                         (G > 1 ? 0.013 * G * L.count : 0.0);
       if (est < best) {
         best = est;
         t.groups = G;
       }
     }
-    t.block0 = blocks;
-    blocks += t.ntx * t.nty * t.ntz * t.groups;
+    if (k > 0) {
+      coarse_blocks += tiles * t.groups;
+      coarse += tiles * (9000.0 * (t.groups - 1) + beside(0, phases) + matrix(0, phases));
+    }
     t.part0 = lat.n_part;
     if (t.groups > 1) lat.n_part += t.groups * L.count;
     lat.t[k] = t;
+  }
+  int blocks = 0;
+  for (int k = 0; k < lat.n; ++k) {
+    msm::LatTile& t = lat.t[k];
+    t.block0 = blocks;
+    blocks += t.ntx * t.nty * t.ntz * t.groups;
   }
 }
 
@@ -668,9 +696,9 @@ void set_anterp_tiles(Geom& g, int target) {
 //    take it always: their grid stages have twice the launches for the short
 //    range to hide behind (9,000 atoms: 139 us, 151 in order).
 //  - The level-0 lattice cutoff beside the coarse levels costs nothing from
-//    about 500 tiles and pays in batches (64 systems as a graph 1402 us, 1416
-//    without; 16 systems 425 and 426; 1,000,000 atoms, 828 tiles: 1135 and 1131;
-//    100,000, 224 tiles: 412 and 407; 24,000, 81 tiles: 145 and 107 as a graph).
+//    about 500 tiles and pays in batches (64 systems as a graph 1372 us, 1386
+//    without; 16 systems 431 and 427; 1,000,000 atoms, 576 tiles: 1126 and 1126;
+//    100,000, 144 tiles: 409 and 408; 24,000, 54 tiles: 146 and 106 as a graph).
 void default_streams(msm::LaunchGeom& L, bool periodic) {
   L.streams = L.lattice0_tiles >= msm::kLattice0SideTiles && !periodic ? 3 : 2;
   L.capture_streams = L.streams;

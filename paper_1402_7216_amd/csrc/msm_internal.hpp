@@ -140,9 +140,9 @@ struct LatTile {
 
 constexpr int kLatMaxHalo = 13;          // tiled kernel handles stencil half-widths up to this
 constexpr int kLatPlanes = 4;            // stencil planes per phase
-// Waves per block: 4 for 4 planes (two blocks per CU where the window allows),
-// two groups of 4 for 6 and 8 planes, whose window leaves room for one block.
-__host__ __device__ constexpr int lat_waves(int b) { return b == 4 ? 4 : 8; }
+// Waves per block: 4 for up to 6 planes (two blocks per CU where the window
+// allows), two groups of 4 for 8 planes, whose window leaves room for one block.
+__host__ __device__ constexpr int lat_waves(int b) { return b == 8 ? 8 : 4; }
 constexpr int kLatMaxPhases = (2 * kLatMaxHalo + kLatPlanes) / kLatPlanes;
 constexpr int kLatMaxGroups = 8;         // phase groups per tile
 constexpr int kLatFragBytes = 3072;      // weight fragment: the three bfloat16 parts of 16 x 32 weights
@@ -155,8 +155,10 @@ struct LatLaunch {
   int phases;              // groups of kLatPlanes stencil planes
   int n2max;               // largest |n|^2 of a tap
   int n_part;              // float64 partials of every grouped level
-  // wave w of a group of 4 takes the row pairs ny = +-cut[phase][w] .. cut[phase][w + 1] - 1
-  unsigned char cut[kLatMaxPhases][8];
+  // wave w of a group of 4 takes a phase's row pairs ny = +-ay for ay = share[phase][w]
+  // up to share[phase][4 + w] - 1, every step[phase]-th
+  unsigned char share[kLatMaxPhases][8];
+  unsigned char step[kLatMaxPhases + 1];
   LatTile t[kMaxLevels];
 };
 

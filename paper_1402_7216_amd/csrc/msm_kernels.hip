@@ -2312,7 +2312,7 @@ __global__ void __launch_bounds__(kBlock) k_lattice(KArgs A, int part) {
 // (cubic, a = 12, h = 2), 3.9e-7 and 3.2e-7 for 9,000 periodic (quintic, a = 10),
 // 6.8e-8 for 1,000 charges; chains of float32 FMAs have 1.07e-6, 6.5e-7 and
 // 4.9e-7, 8.5e-7 and 6.8e-7, 7.0e-8.  (Two float16 parts and three products, 23
-// instead of 31 us at 24,000 atoms, have 1.16e-6, 8.4e-7 and 6.5e-7, 8.5e-7 and
+// instead of 27 us at 24,000 atoms, have 1.16e-6, 8.4e-7 and 6.5e-7, 8.5e-7 and
 // 6.7e-7, 1.5e-7, and lose what is below 2^-38 of a window's largest input.)
 //
 // A block owns 16 x 16 x ZB nodes.  A phase takes 4 planes nz: its input planes
@@ -2320,8 +2320,9 @@ __global__ void __launch_bounds__(kBlock) k_lattice(KArgs A, int part) {
 // (8 values per lane and row, split in registers) serves the 4 planes it is an
 // input of.  The 4 waves split the phase's row pairs.  The weights' fragments
 // come from the L2 (the same for every block).  Bound by the matrix pipe and by
-// staging: with one product of the six, 19 us instead of 31 at 24,000 atoms and
-// 70 instead of 112 at 1M; without the splits 29 and 112.
+// staging: with one product of the six (timing only) 19 us instead of 31 at
+// 24,000 atoms in blocks of 4 planes and 70 instead of 112 at 1M; without the
+// splits 29 and 112.
 // --------------------------------------------------------------------------
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -2502,24 +2503,31 @@ __global__ void __launch_bounds__(ZS * 4 * kWave, 2) k_lattice_mfma(KArgs A, int
       }
     }
   };
-  load_planes(ph0);
+  // a phase's inputs are on their way during the products of the one before,
+  // where that leaves registers
+  constexpr bool kAhead = ZB <= 4;
+  if (kAhead) load_planes(ph0);
 #pragma unroll 1
   for (int ph = ph0; ph < ph1; ++ph) {
     const int nz0 = kLatPlanes * ph - H;
     if (z0 + nz0 + NP <= 0 || z0 + nz0 >= NZ) {         // no input plane lies in the grid
-      if (ph + 1 < ph1) load_planes(ph + 1);
+      if (kAhead && ph + 1 < ph1) load_planes(ph + 1);
       continue;
     }
+    if (!kAhead) load_planes(ph);
     const int zlo = max(0, -(zw + nz0)), zhi = NZ - (zw + nz0);   // the wave's input planes that do
-    // the wave's row pairs ny = +-ay; the plan cuts them into shares of equal cost
-    const int ay0 = uniform(P.cut[ph][wk]), ay1 = uniform(P.cut[ph][wk + 1]);
-    // fragments of the wave's first pair, on their way while the window is staged
+    // the plane of the phase nearest to the centre (the longest rows)
+    const int az = nz0 > 0 ? nz0 : max(0, -(nz0 + kLatPlanes - 1));
+    // the wave's row pairs ny = +-ay
+    const int ay1 = uniform(P.share[ph][4 + wk]), step = uniform(P.step[ph]);
+    int ay = uniform(P.share[ph][wk]);
+    // fragments of the wave's first row pair, on their way while the window is staged
     Split8 a[kLatPlanes];
     auto main_fragments = [&](int ay) {
 #pragma unroll
       for (int j = 0; j < kLatPlanes; ++j) a[j] = fragment(abs(nz0 + j) * H1 + ay);
     };
-    main_fragments(ay0);
+    main_fragments(min(ay, H));
     if (__any(sok && skeep < 8)) {
 #pragma unroll
       for (int p = 0; p < NPT; ++p)
@@ -2537,12 +2545,10 @@ __global__ void __launch_bounds__(ZS * 4 * kWave, 2) k_lattice_mfma(KArgs A, int
         dst[1] = make_float4(v[p][1].v[0], v[p][1].v[1], v[p][1].v[2], v[p][1].v[3]);
       }
     }
-    if (ph + 1 < ph1) load_planes(ph + 1);              // the next phase's inputs, on their way during this one's products
+    if (kAhead && ph + 1 < ph1) load_planes(ph + 1);
     __syncthreads();
-    // the plane of the phase nearest to the centre (the longest rows)
-    const int az = nz0 > 0 ? nz0 : max(0, -(nz0 + kLatPlanes - 1));
 #pragma unroll 1
-    for (int ay = ay0; ay < ay1; ++ay) {
+    for (; ay < ay1; ay += step) {
       Split8 w[2];
       const bool wing = H > 8 && 81 + ay * ay + az * az <= n2max;
       if (wing)
@@ -2556,7 +2562,7 @@ __global__ void __launch_bounds__(ZS * 4 * kWave, 2) k_lattice_mfma(KArgs A, int
       // the wings: the lower half-wave reads input plane zi, the upper one
       // plane zi + 1, so one fragment serves stencil planes 2p and 2p + 1
       if (wing) lat_products<ZB, 2, 2, ZB + 2>(acc, w, win + wing_at + d, win + wing_at - d, plane, zlo - 1, zhi);
-      if (ay + 1 < ay1) main_fragments(ay + 1);          // on their way during the sums
+      if (ay + step < ay1) main_fragments(ay + step);    // on their way during the sums
 #pragma unroll
       for (int z = 0; z < ZB; ++z)
 #pragma unroll
@@ -3632,7 +3638,7 @@ hipError_t launch_eval(int mode, const LaunchGeom& L, hipStream_t s, const Io& i
     if (L.lat_b == 4) {
       MSM_LAT(4, 1);
     } else if (L.lat_b == 6) {
-      MSM_LAT(3, 2);
+      MSM_LAT(6, 1);
     } else if (L.lat_b == 8) {
       MSM_LAT(4, 2);
     } else {
