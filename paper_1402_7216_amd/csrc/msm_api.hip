@@ -690,15 +690,15 @@ void set_anterp_tiles(Geom& g, int target) {
 // stream for another's event 10 to 19, a launch 2.6), which is free only while
 // the device is busy with earlier work, or in a graph.
 //  - Systems whose rows are split finish the short range in 10 to 20 us: all on
-//    one stream (1,000 atoms: 71 us; 74 to 95 with one side stream, 92 to 119
-//    with two; 4,096 ions 75 us per step, 75 to 79, 99).  As a graph one side
-//    stream is right for them too (74 us against 77 and 84), and periodic ones
-//    take it always: their grid stages have twice the launches for the short
-//    range to hide behind (9,000 atoms: 139 us, 151 in order).
+//    one stream (1,000 atoms: 62 us; 70 with one side stream, 87 with two; 4,096
+//    ions 72 us per step, 71, 91).  As a graph one side stream is right for them
+//    too (48 us against 63 and 75), and periodic ones take it always: their grid
+//    stages have twice the launches for the short range to hide behind (9,000
+//    atoms: 123 us, 138 in order; as a graph 117, 135).
 //  - The level-0 lattice cutoff beside the coarse levels costs nothing from
-//    about 500 tiles and pays in batches (64 systems as a graph 1372 us, 1386
-//    without; 16 systems 431 and 427; 1,000,000 atoms, 576 tiles: 1126 and 1126;
-//    100,000, 144 tiles: 409 and 408; 24,000, 54 tiles: 146 and 106 as a graph).
+//    about 500 tiles and pays in batches (64 systems as a graph 1368 us, 1383
+//    without; 16 systems 424 and 426; 1,000,000 atoms, 576 tiles: 1127 and 1126;
+//    50,000, 63 tiles: 597 and 590; 24,000, 54 tiles: 140 and 104 as a graph).
 void default_streams(msm::LaunchGeom& L, bool periodic) {
   L.streams = L.lattice0_tiles >= msm::kLattice0SideTiles && !periodic ? 3 : 2;
   L.capture_streams = L.streams;

@@ -3585,8 +3585,8 @@ hipError_t launch_eval(int mode, const LaunchGeom& L, hipStream_t s, const Io& i
   // blocks is enqueued after the restriction: the host's wait for the fork (10
   // to 19 us) then passes while the device runs what was launched before it,
   // and a graph starts the longer branch, the grid stages, first (24,000 atoms,
-  // 400 blocks, as a graph: 98 us instead of 106).  Where the short range is
-  // the longer branch it goes first (64 systems as a graph: 1311 us, 1356 if
+  // 400 blocks, as a graph: 104 us instead of 107).  Where the short range is
+  // the longer branch it goes first (64 systems as a graph: 1367 us, 1413 if
   // enqueued later).
   const bool later = short_at == 1 && short_side && L.shortr.blocks <= kShortLaterBlocks;
   if (later)
