@@ -240,7 +240,8 @@ double share_rows(msm::LatLaunch& lat, int ph) {
     }
     return true;
   };
-  double cap = 0.5 * std::ceil(2.0 * total / waves);           // costs are multiples of one half
+  // costs are multiples of one half, the first the largest
+  double cap = std::max(cost[0], 0.5 * std::ceil(2.0 * total / waves));
   while (!runs(cap)) cap += 0.5;
   lat.step[ph] = 1;
   const double most = *std::max_element(turn, turn + waves);
